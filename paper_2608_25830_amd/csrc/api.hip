@@ -324,7 +324,7 @@ static gtmp_status check_rrtc(const gtmp_problem *prob, const gtmp_rrtc_opts *o)
     if (!o) return fail(GTMP_EINVAL, "opts is NULL");
     if (o->budget < 1) return fail(GTMP_EINVAL, "budget=%d < 1", o->budget);
     if (o->tree_cap < 2 || o->tree_cap > 4096) return fail(GTMP_EINVAL, "tree_cap=%d outside 2..4096", o->tree_cap);
-    if (gtmp::rrtc_lds_bytes(prob->d, o->tree_cap, 0) > 163840 - 8192)
+    if (gtmp::rrtc_lds_bytes(prob->d, o->tree_cap) > 163840 - 8192)
         return fail(GTMP_EINVAL, "tree_cap=%d needs more than 152 KiB of LDS at d=%d", o->tree_cap, prob->d);
     if (!(o->step > 0.f) || !std::isfinite(o->step)) return fail(GTMP_EINVAL, "step must be finite and > 0");
     if (!(o->resolution > 0.f) || !std::isfinite(o->resolution))

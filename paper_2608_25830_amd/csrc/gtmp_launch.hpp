@@ -172,10 +172,10 @@ hipError_t launch_simplify(const ArmParams *arm, const SceneParams &scene, int w
 
 // ---- RRT-Connect local planner (rrtc.hip)
 struct RrtcPlan {
-    size_t off_counters, off_vfree, off_cand, total;
+    size_t off_counters, off_grid, off_params, off_vfree, off_cand, total;
 };
 RrtcPlan make_rrtc_plan(const gtmp_problem &p);
-size_t rrtc_lds_bytes(int d, int cap, int obstacle_floats);
+size_t rrtc_lds_bytes(int d, int cap);
 hipError_t launch_rrtc_repair(const gtmp_problem &p, const ArmParams *arm, const SceneParams &S, int wdim,
                               const float *q0, const float *goals, const float *Q, float *C_s, float *C_h, float *C_l,
                               uint8_t *flags, uint64_t seed, uint64_t stage, const gtmp_rrtc_opts &o, void *workspace,
