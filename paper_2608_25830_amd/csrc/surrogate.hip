@@ -54,136 +54,6 @@ __device__ __forceinline__ uint16_t d2bf(double x) {
     return (uint16_t)(__float_as_uint((float)__longlong_as_double((long long)u)) >> 16);
 }
 
-// One thread per configuration: [q/pi, sin(2 pi B q/pi), cos(2 pi B q/pi), 0...]
-// in FP64, rounded to BF16 once, 64 values.  FP64 keeps the phases (up to a
-// few tens of radians) accurate enough that the BF16 rounding of a feature
-// does not depend on how its value was computed.
-__global__ void __launch_bounds__(256) k_features(int d, int64_t n, const float *__restrict__ X,
-                                                  const float *__restrict__ Bf, uint16_t *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    constexpr double kPi = 3.14159265358979323846;
-    double qh[GTMP_MAX_DOF];
-    for (int j = 0; j < GTMP_MAX_DOF; ++j) qh[j] = j < d ? (double)X[i * d + j] / kPi : 0.0;
-    uint16_t v[GTMP_SUR_IN];
-#pragma unroll
-    for (int k = 0; k < GTMP_SUR_IN; ++k) v[k] = 0;
-    for (int j = 0; j < d; ++j) v[j] = d2bf(qh[j]);
-    for (int f = 0; f < GTMP_SUR_FREQ; ++f) {
-        double s = 0.0;
-        for (int j = 0; j < d; ++j) s += (double)Bf[f * d + j] * qh[j];
-        s *= 2.0 * kPi;
-        double sn, cs;
-        sincos(s, &sn, &cs);
-        v[d + f] = d2bf(sn);
-        v[d + GTMP_SUR_FREQ + f] = d2bf(cs);
-    }
-    uint4 *dst = reinterpret_cast<uint4 *>(out + i * GTMP_SUR_IN);
-#pragma unroll
-    for (int q = 0; q < GTMP_SUR_IN / 8; ++q) {
-        uint4 w;
-        w.x = v[8 * q + 0] | ((uint32_t)v[8 * q + 1] << 16);
-        w.y = v[8 * q + 2] | ((uint32_t)v[8 * q + 3] << 16);
-        w.z = v[8 * q + 4] | ((uint32_t)v[8 * q + 5] << 16);
-        w.w = v[8 * q + 6] | ((uint32_t)v[8 * q + 7] << 16);
-        dst[q] = w;
-    }
-}
-
-// ------------------------------------------------------------------ GEMM (NT)
-// C[m][n] = sum_k A[m][k] B[n][k], A and B BF16 row-major with K contiguous,
-// K a multiple of 32 (per split).  Block tile 128 x 128, four waves of
-// 64 x 64 (2 x 2 MFMA 32x32x16 tiles), K step 32 staged through LDS.
-enum GemmEpi { EPI_F32 = 0, EPI_BIAS_RELU_BF16 = 1, EPI_MASK_BF16 = 2 };
-
-constexpr int kBM = 128, kBN = 128, kBK = 32, kLdsPad = 8;
-constexpr int kLdsRow = kBK + kLdsPad;  // 40 BF16 = 80 bytes per row
-
-template <int EPI>
-__global__ void __launch_bounds__(256) k_gemm_nt(int M, int N, int K_split, const uint16_t *__restrict__ A, int lda,
-                                                 const uint16_t *__restrict__ B, int ldb, void *__restrict__ Cout,
-                                                 int ldc, const float *__restrict__ bias,
-                                                 const uint16_t *__restrict__ mask, int ldm, size_t c_split_stride) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[kBM * kLdsRow];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[kBN * kLdsRow];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * kBM, n0 = blockIdx.x * kBN;
-    const int k_begin = blockIdx.z * K_split;
-    // global -> LDS: thread loads 16 BF16 (2 x 16 B) of one row of A and of B
-    const int lr = tid >> 1, lk = (tid & 1) * 16;
-    const bool a_ok = m0 + lr < M, b_ok = n0 + lr < N;
-    const uint16_t *a_src = A + (size_t)(a_ok ? m0 + lr : 0) * lda + k_begin + lk;
-    const uint16_t *b_src = B + (size_t)(b_ok ? n0 + lr : 0) * ldb + k_begin + lk;
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const uint4 zero4 = make_uint4(0u, 0u, 0u, 0u);
-    for (int k0 = 0; k0 < K_split; k0 += kBK) {
-        const uint4 a0 = a_ok ? *reinterpret_cast<const uint4 *>(a_src + k0) : zero4;
-        const uint4 a1 = a_ok ? *reinterpret_cast<const uint4 *>(a_src + k0 + 8) : zero4;
-        const uint4 b0 = b_ok ? *reinterpret_cast<const uint4 *>(b_src + k0) : zero4;
-        const uint4 b1 = b_ok ? *reinterpret_cast<const uint4 *>(b_src + k0 + 8) : zero4;
-        __syncthreads();  // previous tile fully consumed
-        *reinterpret_cast<uint4 *>(&As[lr * kLdsRow + lk]) = a0;
-        *reinterpret_cast<uint4 *>(&As[lr * kLdsRow + lk + 8]) = a1;
-        *reinterpret_cast<uint4 *>(&Bs[lr * kLdsRow + lk]) = b0;
-        *reinterpret_cast<uint4 *>(&Bs[lr * kLdsRow + lk + 8]) = b1;
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < kBK / 16; ++s) {
-            const int kk = 16 * s + 8 * (lane >> 5);
-            bf16x8 af[2], bfr[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = wm * 64 + 32 * i + (lane & 31);
-                af[i] = *reinterpret_cast<const bf16x8 *>(&As[r * kLdsRow + kk]);
-            }
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int r = wn * 64 + 32 * j + (lane & 31);
-                bfr[j] = *reinterpret_cast<const bf16x8 *>(&Bs[r * kLdsRow + kk]);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-        }
-    }
-    // epilogue: element v of tile (i, j) is row 8 (v/4) + 4 (lane/32) + v%4, column lane%32
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int col = n0 + wn * 64 + 32 * j + (lane & 31);
-            if (col >= N) continue;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = m0 + wm * 64 + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (row >= M) continue;
-                const float x = acc[i][j][v];
-                if constexpr (EPI == EPI_F32) {
-                    float *C = static_cast<float *>(Cout) + blockIdx.z * c_split_stride;
-                    C[(size_t)row * ldc + col] = x;
-                } else if constexpr (EPI == EPI_BIAS_RELU_BF16) {
-                    const float z = x + bias[col];
-                    static_cast<uint16_t *>(Cout)[(size_t)row * ldc + col] = f2bf(z > 0.f ? z : 0.f);
-                } else {
-                    const bool on = bf2f(mask[(size_t)row * ldm + col]) > 0.f;
-                    static_cast<uint16_t *>(Cout)[(size_t)row * ldc + col] = f2bf(on ? x : 0.f);
-                }
-            }
-        }
-}
-
 // ------------------------------------------------------------------ fused inference
 // Whole network for 128 rows per block tile (inference only): features
 // computed in FP64 straight into LDS, then four hidden layers whose BF16
@@ -195,8 +65,7 @@ __global__ void __launch_bounds__(256) k_gemm_nt(int M, int N, int K_split, cons
 // 32-column tile and 16-wide K slice, the 64 lanes' 16-byte operands side by
 // side), so each weight load of a wave is one contiguous 1 KB read from L2.
 // Two blocks share a CU (2 x 68 KB of LDS), so one block's feature or
-// epilogue phase overlaps the other's MFMAs.  Sums run in K order as in
-// k_gemm_nt.
+// epilogue phase overlaps the other's MFMAs.  Sums run in K order.
 constexpr int kFR = 128;                              // rows per block tile
 constexpr int kFRow = GTMP_SUR_WIDTH + 8;             // LDS row stride (BF16), 528 bytes
 constexpr int kColTiles = GTMP_SUR_WIDTH / 32;        // 32-column output tiles per layer
@@ -636,95 +505,426 @@ __global__ void __launch_bounds__(256, 2) k_mlp_prune(int d, int M, int N, int G
     }
 }
 
-// ------------------------------------------------------------------ small kernels
-// out [C][R] = in [R][C]^T, BF16, R and C multiples of 64.
-__global__ void __launch_bounds__(256) k_transpose_bf16(int R, int C, const uint16_t *__restrict__ in,
-                                                        uint16_t *__restrict__ out) {
-    __shared__ uint16_t t[64][65];
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int r = ty; r < 64; r += 4) t[r][tx] = in[(size_t)(r0 + r) * C + c0 + tx];
+// ------------------------------------------------------------------ training
+// One step's loss and gradient in four launches (weight fragments, rows, weight
+// gradients, sums).  A batch of 8192 rows is 10.5 GFLOP and a few megabytes,
+// microseconds of either, so a step is bound by launches and by how often the
+// activations cross memory: the layer-by-layer form (products, transposes,
+// column sums and split sums one after another, 42 launches) took 596 us of
+// kernel time for 8192 rows; these take 51 (rows 25, weight gradients 13, sums
+// 5, Adam 4, fragments 3).
+//
+// k_train_rows takes kTR rows through the whole network and back in one block:
+// the activations of every layer stay in LDS, each gradient dZ_l overwrites
+// the activations it masks.  kTR = 32 puts 8192 rows on 256 CUs; eight waves
+// share the 256 columns of a layer, a 32 x 32 tile each, the weights read from
+// L2 in fragment order (forward and transposed copies).  What the weight
+// gradients need, A_{l-1} and dZ_l, leaves the block once, as slabs in MFMA
+// operand order of the product over the batch (per 32 columns and 16 rows the
+// 64 lanes' 16-byte operands side by side: lane holds rows 8 (lane / 32) ..+8
+// of column lane % 32), so k_train_weights reads its fragments with contiguous
+// 1 KB loads, without LDS or transposes (with slabs [column][row], whose
+// loads touch twice the lines, it took 18 us instead of 13).  Sums over rows (biases, output layer, loss) leave as one
+// partial per half slab and are added in slab order.
+// Every layer's sums run over K in the order of the inference kernels' MFMAs.
+constexpr int kTR = 32;
+constexpr int kTRow0 = GTMP_SUR_IN + 8;      // LDS row strides (BF16)
+constexpr int kTRow = GTMP_SUR_WIDTH + 8;
+constexpr int kTSplit = 8;                   // batch splits of the weight gradients
+constexpr int kTVec = 5;                     // column sums per half slab: w5, b4, b3, b2, b1
+
+// Backward fragments of layers 2..4 (l = 1..3): W_l transposed.
+constexpr int kBackLayer = kColTiles * (GTMP_SUR_WIDTH / 16) * 64;
+
+// Forward fragments as k_weight_frag lays them out but with layer 1's columns
+// in the standard feature order, then the backward ones: lane's operand of
+// (column tile c, K slice ks) is W_l[16 ks + 8 (lane / 32) ..+8][32 c + lane % 32].
+__global__ void __launch_bounds__(256) k_train_frag(const uint16_t *__restrict__ P16, SurLayout L,
+                                                    uint4 *__restrict__ Wf, uint4 *__restrict__ Wb) {
+    const int f = blockIdx.x * blockDim.x + threadIdx.x;
+    if (f < kFragTotal) {
+        const int l = f < frag_offset(1) ? 0 : 1 + (f - frag_offset(1)) / (frag_offset(2) - frag_offset(1));
+        const int K = l == 0 ? GTMP_SUR_IN : GTMP_SUR_WIDTH, S = K / 16;
+        const int r = f - frag_offset(l);
+        const int lane = r & 63, ks = (r >> 6) % S, c = (r >> 6) / S;
+        Wf[f] = *reinterpret_cast<const uint4 *>(P16 + L.W[l] + (size_t)(32 * c + (lane & 31)) * K + 16 * ks +
+                                                 8 * (lane >> 5));
+        return;
+    }
+    const int b = f - kFragTotal;
+    if (b >= 3 * kBackLayer) return;
+    const int l = 1 + b / kBackLayer, r = b % kBackLayer;
+    const int lane = r & 63, ks = (r >> 6) % (GTMP_SUR_WIDTH / 16), c = (r >> 6) / (GTMP_SUR_WIDTH / 16);
+    const uint16_t *src = P16 + L.W[l] + (size_t)(16 * ks + 8 * (lane >> 5)) * GTMP_SUR_WIDTH + 32 * c + (lane & 31);
+    uint16_t w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = src[(size_t)i * GTMP_SUR_WIDTH];
+    Wb[b] = make_uint4(pack2(w[0], w[1]), pack2(w[2], w[3]), pack2(w[4], w[5]), pack2(w[6], w[7]));
+}
+
+// A wave's weight fragments of one layer (its 32 columns), requested before
+// the barrier that ends the layer before: a read of the weights goes past the
+// XCD's L2 once per step, several layers' worth of MFMAs away.
+template <int K>
+struct TrainW {
+    bf16x8 w[K / 16];
+    __device__ __forceinline__ TrainW(const bf16x8 *__restrict__ W, int wave, int lane) {
+#pragma unroll
+        for (int k = 0; k < K / 16; ++k) w[k] = W[((size_t)wave * (K / 16) + k) * 64 + lane];
+    }
+};
+
+// The wave's 32 output columns of in [kTR][K] (LDS, row stride RS): element v
+// of the result is column 8 (v/4) + 4 (lane/32) + v%4 of the tile, row lane%32.
+template <int K, int RS>
+__device__ __forceinline__ f32x16 train_tile(const TrainW<K> &W, const uint16_t *in, int lane) {
+    constexpr int S = K / 16;
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    const uint16_t *a = in + (lane & 31) * RS + 8 * (lane >> 5);
+#pragma unroll
+    for (int k = 0; k < S; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(W.w[k], *reinterpret_cast<const bf16x8 *>(a + 16 * k), acc, 0, 0, 0);
+    return acc;
+}
+
+__device__ __forceinline__ uint2 pack4(const uint16_t (&h)[4]) { return make_uint2(pack2(h[0], h[1]), pack2(h[2], h[3])); }
+
+// out = bf16(relu(in W^T + bias)), the wave's columns.
+template <int K, int RS>
+__device__ __forceinline__ void train_forward(const TrainW<K> &W, const float *__restrict__ bias, const uint16_t *in,
+                                              uint16_t *out, int wave, int lane) {
+    const f32x16 acc = train_tile<K, RS>(W, in, lane);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int col = 32 * wave + 8 * g + 4 * (lane >> 5);
+        uint16_t h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float z = acc[4 * g + r] + bias[col + r];
+            h[r] = f2bf(z > 0.f ? z : 0.f);
+        }
+        *reinterpret_cast<uint2 *>(&out[(lane & 31) * kTRow + col]) = pack4(h);
+    }
+}
+
+// act = bf16((dZ W) * [act > 0]), the wave's columns, in place.
+__device__ __forceinline__ void train_backward(const TrainW<GTMP_SUR_WIDTH> &W, const uint16_t *dZ, uint16_t *act, int wave,
+                                               int lane) {
+    const f32x16 acc = train_tile<GTMP_SUR_WIDTH, kTRow>(W, dZ, lane);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        uint2 *p = reinterpret_cast<uint2 *>(&act[(lane & 31) * kTRow + 32 * wave + 8 * g + 4 * (lane >> 5)]);
+        const uint2 m = *p;
+        const uint32_t mw[2] = {m.x, m.y};
+        uint16_t h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool on = bf2f((uint16_t)(mw[r >> 1] >> (16 * (r & 1)))) > 0.f;
+            h[r] = f2bf(on ? acc[4 * g + r] : 0.f);
+        }
+        *p = pack4(h);
+    }
+}
+
+// Half a column of t (16 rows from row 16 half) into its slab.
+template <int RS>
+__device__ __forceinline__ void read_half_column(const uint16_t *t, int c, int half, uint16_t (&h)[16]) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) h[r] = t[(16 * half + r) * RS + c];
+}
+__device__ __forceinline__ void store_half_column(uint16_t *slab, int c, int half, const uint16_t (&h)[16]) {
+    uint4 *dst = reinterpret_cast<uint4 *>(slab) + ((c >> 5) * 2 + half) * 64 + (c & 31);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        dst[32 * q] = make_uint4(pack2(h[8 * q], h[8 * q + 1]), pack2(h[8 * q + 2], h[8 * q + 3]),
+                            pack2(h[8 * q + 4], h[8 * q + 5]), pack2(h[8 * q + 6], h[8 * q + 7]));
+}
+
+struct TrainBufs {
+    uint4 *Wf, *Wb;
+    uint16_t *X0, *A[3], *dZ[4];  // slabs: features, activations 1..3, gradients 1..4
+    float *col;                   // [slab][half][kTVec][256]
+    float *row;                   // [slab][2]: loss terms, dz
+    float *part;                  // [kTSplit][weights]
+    size_t total;
+};
+
+__global__ void __launch_bounds__(512, 2) k_train_rows(int d, const float *__restrict__ X, const uint8_t *__restrict__ y,
+                                                       const float *__restrict__ Bf, const uint16_t *__restrict__ P16,
+                                                       const float *__restrict__ P32, SurLayout L, float inv_n,
+                                                       float *__restrict__ logits, TrainBufs T) {
+    __shared__ __attribute__((aligned(16))) uint16_t x0[kTR * kTRow0];
+    __shared__ __attribute__((aligned(16))) uint16_t act[4][kTR * kTRow];
+    __shared__ float dz_s[kTR], loss_s[kTR];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = tid & 255, half = tid >> 8;
+    const size_t slab = blockIdx.x, row0 = slab * kTR;
+    const bf16x8 *Wf = reinterpret_cast<const bf16x8 *>(T.Wf), *Wb = reinterpret_cast<const bf16x8 *>(T.Wb);
+    const TrainW<GTMP_SUR_IN> w1(Wf + frag_offset(0), wave, lane);
+    const TrainW<GTMP_SUR_WIDTH> w2(Wf + frag_offset(1), wave, lane);
+    {  // features: a thread per (row, frequency), the first d also the linear ones
+        constexpr double kPi = 3.14159265358979323846;
+        const int r = tid >> 4, f = tid & 15;
+        const float *x = X + (row0 + r) * d;
+        double qh[GTMP_MAX_DOF];
+        for (int j = 0; j < GTMP_MAX_DOF; ++j) qh[j] = j < d ? (double)x[j] / kPi : 0.0;
+        double s = 0.0;
+        for (int j = 0; j < d; ++j) s += (double)Bf[f * d + j] * qh[j];
+        s *= 2.0 * kPi;
+        double sn, cs;
+        sincos(s, &sn, &cs);
+        uint16_t *o = x0 + r * kTRow0;
+        o[d + f] = d2bf(sn);
+        o[d + GTMP_SUR_FREQ + f] = d2bf(cs);
+        for (int j = 0; j < GTMP_MAX_DOF; ++j)
+            if (j == f && j < d) o[j] = d2bf(qh[j]);
+        for (int k = d + 2 * GTMP_SUR_FREQ + f; k < GTMP_SUR_IN; k += 16) o[k] = 0;
+    }
     __syncthreads();
-    for (int c = ty; c < 64; c += 4) out[(size_t)(c0 + c) * R + r0 + tx] = t[tx][c];
-}
-
-// Output layer, loss and its gradient: one wave per row.
-//   z = sum_k bf16(w5)[k] a4[k] + b5;  loss_b = max(z,0) - y z + log1p(exp(-|z|));
-//   dz = (sigmoid(z) - y) / n
-__global__ void __launch_bounds__(256) k_head(int64_t n, const uint16_t *__restrict__ A4,
-                                              const uint16_t *__restrict__ w5, const float *__restrict__ b5,
-                                              const uint8_t *__restrict__ y, float inv_n, float *__restrict__ logits,
-                                              float *__restrict__ loss_terms, float *__restrict__ dz) {
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (row >= n) return;
-    const int lane = lane_id();
-    const uint16_t *a = A4 + row * GTMP_SUR_WIDTH;
-    float s = 0.f;
+    if (tid < 2 * GTMP_SUR_IN) {
+        uint16_t h[16];
+        read_half_column<kTRow0>(x0, tid & (GTMP_SUR_IN - 1), tid / GTMP_SUR_IN, h);
+        store_half_column(T.X0 + slab * kTR * GTMP_SUR_IN, tid & (GTMP_SUR_IN - 1), tid / GTMP_SUR_IN, h);
+    }
+    const size_t so = slab * kTR * GTMP_SUR_WIDTH;
+    auto put = [&](const uint16_t *t, uint16_t *dst) {
+        uint16_t h[16];
+        read_half_column<kTRow>(t, c, half, h);
+        store_half_column(dst + so, c, half, h);
+    };
+    train_forward<GTMP_SUR_IN, kTRow0>(w1, P32 + L.b[0], x0, act[0], wave, lane);
+    const TrainW<GTMP_SUR_WIDTH> w3(Wf + frag_offset(2), wave, lane);
+    __syncthreads();
+    train_forward<GTMP_SUR_WIDTH, kTRow>(w2, P32 + L.b[1], act[0], act[1], wave, lane);
+    const TrainW<GTMP_SUR_WIDTH> w4(Wf + frag_offset(3), wave, lane);
+    put(act[0], T.A[0]);
+    __syncthreads();
+    train_forward<GTMP_SUR_WIDTH, kTRow>(w3, P32 + L.b[2], act[1], act[2], wave, lane);
+    const TrainW<GTMP_SUR_WIDTH> v4(Wb + 2 * kBackLayer, wave, lane);
+    put(act[1], T.A[1]);
+    __syncthreads();
+    train_forward<GTMP_SUR_WIDTH, kTRow>(w4, P32 + L.b[3], act[2], act[3], wave, lane);
+    const TrainW<GTMP_SUR_WIDTH> v3(Wb + kBackLayer, wave, lane);
+    put(act[2], T.A[2]);
+    __syncthreads();
+    // output layer, loss and its gradient: a wave per row, four products a lane
+    //   z = sum_k bf16(w5)[k] a4[k] + b5;  loss_b = max(z,0) - y z + log1p(exp(-|z|));
+    //   dz = (sigmoid(z) - y) / n
+    for (int r = wave; r < kTR; r += 8) {
+        const uint16_t *a = act[3] + r * kTRow;
+        float s = 0.f;
 #pragma unroll
-    for (int q = 0; q < GTMP_SUR_WIDTH / kWave; ++q) {
-        const int k = lane * (GTMP_SUR_WIDTH / kWave) + q;
-        s = __builtin_fmaf(bf2f(w5[k]), bf2f(a[k]), s);
+        for (int q = 0; q < GTMP_SUR_WIDTH / kWave; ++q) {
+            const int k = lane * (GTMP_SUR_WIDTH / kWave) + q;
+            s = __builtin_fmaf(bf2f(P16[L.w5 + k]), bf2f(a[k]), s);
+        }
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) {
+            const float z = s + P32[L.b5];
+            if (logits) logits[row0 + r] = z;
+            const float yy = y[row0 + r] ? 1.f : 0.f;
+            const float az = __builtin_fabsf(z);
+            const float e = __expf(-az);
+            loss_s[r] = (z > 0.f ? z : 0.f) - yy * z + log1pf(e);
+            const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
+            dz_s[r] = (sig - yy) * inv_n;
+        }
+    }
+    __syncthreads();
+    float *col = T.col + ((2 * slab + half) * kTVec) * GTMP_SUR_WIDTH + c;
+    {  // dw5's part, then dZ4 = bf16(dz[b] bf16(w5)[k] [a4 > 0]) over a4, its column sum and slab
+        const float wk = bf2f(P16[L.w5 + c]);
+        uint16_t h[16];
+        float sw = 0.f, sb = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            uint16_t *p = &act[3][(16 * half + r) * kTRow + c];
+            const float a = bf2f(*p), g = dz_s[16 * half + r];
+            sw = __builtin_fmaf(g, a, sw);
+            h[r] = f2bf(a > 0.f ? g * wk : 0.f);
+            *p = h[r];
+            sb += bf2f(h[r]);
+        }
+        col[0] = sw;
+        col[GTMP_SUR_WIDTH] = sb;
+        store_half_column(T.dZ[3] + so, c, half, h);
+        if (wave == 0) {
+            float a = lane < kTR ? loss_s[lane] : 0.f, b = lane < kTR ? dz_s[lane] : 0.f;
+#pragma unroll
+            for (int off = kTR / 2; off > 0; off >>= 1) {
+                a += __shfl_xor(a, off);
+                b += __shfl_xor(b, off);
+            }
+            if (lane == 0) {
+                T.row[2 * slab] = a;
+                T.row[2 * slab + 1] = b;
+            }
+        }
+    }
+    __syncthreads();
+    auto finish = [&](int l) {  // slab and column sum of dZ_{l+1}, in act[l]
+        uint16_t h[16];
+        read_half_column<kTRow>(act[l], c, half, h);
+        store_half_column(T.dZ[l] + so, c, half, h);
+        float sb = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sb += bf2f(h[r]);
+        col[(4 - l) * GTMP_SUR_WIDTH] = sb;
+    };
+    train_backward(v4, act[3], act[2], wave, lane);
+    const TrainW<GTMP_SUR_WIDTH> v2(Wb, wave, lane);
+    __syncthreads();
+    train_backward(v3, act[2], act[1], wave, lane);
+    finish(2);
+    __syncthreads();
+    train_backward(v2, act[1], act[0], wave, lane);
+    finish(1);
+    __syncthreads();
+    finish(0);
+}
+
+// dW_l = dZ_l^T A_{l-1} over a split of the slabs, a 64 x 128 tile (layer 1:
+// 64 x 64) per block of four waves, 32 x 64 (32 x 32) each; a slab's
+// fragments are requested kTAhead slabs ahead.  Split k takes every kTSplit-th
+// slab from k, and its blocks are the ones of index k modulo kTSplit: blocks
+// are dealt to the eight XCDs in turn, so the XCD that wrote a slab reads it
+// again, and each XCD reads an eighth of the slabs (splits of consecutive
+// slabs over consecutive blocks, every XCD reading all of them, took 20 us).
+// Tiles (64 x 128) rather
+// than 128 x 128 so that eight splits, whose partials are 6.8 MB to write and
+// add, already make 224 blocks.
+constexpr int kTWeights = GTMP_SUR_WIDTH * GTMP_SUR_IN + 3 * GTMP_SUR_WIDTH * GTMP_SUR_WIDTH;
+__host__ __device__ constexpr int train_part_offset(int l) {
+    return l == 0 ? 0 : GTMP_SUR_WIDTH * GTMP_SUR_IN + (l - 1) * GTMP_SUR_WIDTH * GTMP_SUR_WIDTH;
+}
+constexpr int kTTiles = 4 + 3 * 8;  // blocks per split
+constexpr int kTAhead = 4;          // slabs of fragments in flight per wave
+
+template <int NJ>
+__device__ __forceinline__ void train_weight_tile(const uint16_t *__restrict__ dZ, const uint16_t *__restrict__ Ap,
+                                                  int K_in, int m0, int n0, size_t slab0, int slabs, float *out,
+                                                  int lane) {
+    const int cl = lane & 31;
+    f32x16 acc[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    // in 16-byte fragments: a slab holds kTR / 8 of each column
+    const bf16x8 *pa = reinterpret_cast<const bf16x8 *>(dZ) + (slab0 * GTMP_SUR_WIDTH + m0) * (kTR / 8) + lane;
+    const bf16x8 *pb = reinterpret_cast<const bf16x8 *>(Ap) + (slab0 * K_in + n0) * (kTR / 8) + lane;
+    const size_t sa = (size_t)kTSplit * (kTR / 8) * GTMP_SUR_WIDTH, sb = (size_t)kTSplit * (kTR / 8) * K_in;
+    bf16x8 a[kTAhead][2], b[kTAhead][NJ][2];
+    auto load = [&](int q, int s) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            a[q][k] = pa[s * sa + 64 * k];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) b[q][j][k] = pb[s * sb + 128 * j + 64 * k];
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < kTAhead; ++q) load(q, q < slabs ? q : 0);
+    for (int s0 = 0; s0 < slabs; s0 += kTAhead) {
+#pragma unroll
+        for (int q = 0; q < kTAhead; ++q) {
+            if (s0 + q < slabs) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[q][k], b[q][j][k], acc[j], 0, 0, 0);
+            }
+            const int nx = s0 + q + kTAhead;
+            load(q, nx < slabs ? nx : 0);
+        }
     }
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane != 0) return;
-    const float z = s + b5[0];
-    if (logits) logits[row] = z;
-    if (y) {
-        const float yy = y[row] ? 1.f : 0.f;
-        const float az = __builtin_fabsf(z);
-        const float e = __expf(-az);
-        loss_terms[row] = (z > 0.f ? z : 0.f) - yy * z + log1pf(e);
-        const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-        dz[row] = (sig - yy) * inv_n;
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            out[(size_t)(m0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * K_in + n0 + 32 * j + cl] = acc[j][v];
+}
+
+__global__ void __launch_bounds__(256) k_train_weights(int slabs_per_split, TrainBufs T) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int split = blockIdx.x % kTSplit, t = blockIdx.x / kTSplit;
+    const size_t slab0 = (size_t)split;
+    float *part = T.part + (size_t)split * kTWeights;
+    if (t < 4) {  // layer 1: 256 x 64
+        train_weight_tile<1>(T.dZ[0], T.X0, GTMP_SUR_IN, 64 * t + 32 * (wave >> 1), 32 * (wave & 1), slab0,
+                             slabs_per_split, part + train_part_offset(0), lane);
+        return;
+    }
+    const int l = 1 + (t - 4) / 8, q = (t - 4) % 8;
+    const uint16_t *dZ = l == 1 ? T.dZ[1] : l == 2 ? T.dZ[2] : T.dZ[3];
+    const uint16_t *Ap = l == 1 ? T.A[0] : l == 2 ? T.A[1] : T.A[2];
+    train_weight_tile<2>(dZ, Ap, GTMP_SUR_WIDTH, 64 * (q >> 1) + 32 * (wave >> 1), 128 * (q & 1) + 64 * (wave & 1),
+                         slab0, slabs_per_split, part + train_part_offset(l), lane);
+}
+
+// The partials added in their order: weights (a thread per entry), then the
+// column sums (16 columns per block, the half slabs in 16 runs), then the
+// loss and db5.
+constexpr int kTSumWeights = kTWeights / 256, kTSumCols = kTVec * GTMP_SUR_WIDTH / 16;
+static_assert(kTWeights % 256 == 0, "whole blocks of weights");
+
+__global__ void __launch_bounds__(256) k_train_sums(int slabs, SurLayout L, float inv_n, TrainBufs T,
+                                                    float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ float sh[2][256];
+    const int tid = threadIdx.x, b = blockIdx.x;
+    if (b < kTSumWeights) {
+        const int i = b * 256 + tid;
+        float p[kTSplit];
+#pragma unroll
+        for (int k = 0; k < kTSplit; ++k) p[k] = T.part[(size_t)k * kTWeights + i];
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < kTSplit; ++k) s += p[k];
+        const int l = i < train_part_offset(1) ? 0 : 1 + (i - train_part_offset(1)) / (GTMP_SUR_WIDTH * GTMP_SUR_WIDTH);
+        grad[L.W[l] + i - train_part_offset(l)] = s;
+        return;
+    }
+    if (b < kTSumWeights + kTSumCols) {
+        const int c = (b - kTSumWeights) * 16 + (tid & 15), run = tid >> 4;  // c: vector * 256 + column
+        const int per = slabs / 8;                                          // 2 slabs / 16 runs
+        const float *p = T.col + (size_t)run * per * kTVec * GTMP_SUR_WIDTH + c;
+        float s = 0.f;
+#pragma unroll 8
+        for (int k = 0; k < per; ++k) s += p[(size_t)k * kTVec * GTMP_SUR_WIDTH];
+        sh[0][tid] = s;
+        __syncthreads();
+        if (run == 0) {
+            for (int r = 1; r < 16; ++r) s += sh[0][16 * r + tid];
+            const int v = c / GTMP_SUR_WIDTH, k = c % GTMP_SUR_WIDTH;
+            grad[(v == 0 ? L.w5 : L.b[4 - v]) + k] = s;
+        }
+        return;
+    }
+    float a = 0.f, z = 0.f;
+    for (int k = tid; k < slabs; k += 256) {
+        a += T.row[2 * k];
+        z += T.row[2 * k + 1];
+    }
+    sh[0][tid] = a;
+    sh[1][tid] = z;
+    for (int h = 128; h > 0; h >>= 1) {
+        __syncthreads();
+        if (tid < h) {
+            sh[0][tid] += sh[0][tid + h];
+            sh[1][tid] += sh[1][tid + h];
+        }
+    }
+    if (tid == 0) {
+        *loss = sh[0][0] * inv_n;
+        grad[L.b5] = sh[1][0];
     }
 }
 
-// dZ4 = bf16(dz[b] bf16(w5)[k] [a4 > 0])
-__global__ void __launch_bounds__(256) k_head_back(int64_t n, const float *__restrict__ dz,
-                                                   const uint16_t *__restrict__ w5, const uint16_t *__restrict__ A4,
-                                                   uint16_t *__restrict__ dZ) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * GTMP_SUR_WIDTH) return;
-    const int64_t b = i / GTMP_SUR_WIDTH;
-    const int k = (int)(i % GTMP_SUR_WIDTH);
-    const float g = dz[b] * bf2f(w5[k]);
-    dZ[i] = f2bf(bf2f(A4[i]) > 0.f ? g : 0.f);
-}
-
-// Column sums over fixed row chunks: part[p][c] = sum_{r in chunk p} scale[r] X[r][c]
-template <typename T>
-__device__ __forceinline__ float load_val(const T *p);
-template <>
-__device__ __forceinline__ float load_val<uint16_t>(const uint16_t *p) { return bf2f(*p); }
-template <>
-__device__ __forceinline__ float load_val<float>(const float *p) { return *p; }
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_colsum_part(int64_t rows, int cols, int rows_per_part, const T *__restrict__ X,
-                                                     const float *__restrict__ scale, float *__restrict__ part) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_part;
-    const int64_t r1 = r0 + rows_per_part < rows ? r0 + rows_per_part : rows;
-    float s = 0.f;
-    for (int64_t r = r0; r < r1; ++r) {
-        const float x = load_val<T>(X + r * cols + c);
-        s = scale ? __builtin_fmaf(scale[r], x, s) : s + x;
-    }
-    part[(size_t)blockIdx.y * cols + c] = s;
-}
-
-// out[i] = sum_p part[p][i] in p order
-__global__ void __launch_bounds__(256) k_sum_parts(int parts, int64_t len, const float *__restrict__ part,
-                                                   float *__restrict__ out, float scale) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= len) return;
-    float s = 0.f;
-    for (int p = 0; p < parts; ++p) s += part[(size_t)p * len + i];
-    out[i] = s * scale;
-}
-
+// ------------------------------------------------------------------ small kernels
 __global__ void __launch_bounds__(256) k_adam(int total, float *__restrict__ P, uint16_t *__restrict__ P16,
                                               const float *__restrict__ g, float *__restrict__ m,
                                               float *__restrict__ v, float lr, float b1, float b2, float eps,
@@ -781,44 +981,30 @@ __global__ void __launch_bounds__(256) k_label_states(int d, int64_t n, int H, u
 // ------------------------------------------------------------------ host side
 static unsigned blocks_for(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
 
-template <int EPI>
-static void gemm(int M, int N, int K, int splits, const uint16_t *A, int lda, const uint16_t *B, int ldb, void *C,
-                 int ldc, const float *bias, const uint16_t *mask, int ldm, hipStream_t s) {
-    const dim3 grid((unsigned)((N + kBN - 1) / kBN), (unsigned)((M + kBM - 1) / kBM), (unsigned)splits);
-    hipLaunchKernelGGL(k_gemm_nt<EPI>, grid, dim3(256), 0, s, M, N, K / splits, A, lda, B, ldb, C, ldc, bias, mask,
-                       ldm, (size_t)M * ldc);
-}
-
-// Workspace carve-up for n rows.
+// Workspace carve-up of the inference calls.
 struct SurWs {
-    uint4 *Wf;  // fragment-order weights (inference)
-    uint16_t *X0, *A[4], *dZa, *dZb, *T1, *T2, *WT;
-    float *part, *loss_terms, *dz, *logit_tmp, *Xf;
+    uint4 *Wf;  // fragment-order weights
+    uint16_t *X0, *A[4];
+    float *logit_tmp, *Xf;
     size_t total;
 };
 static size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
-constexpr int kSplitsMax = 32;      // split-K partials of the weight gradients
-constexpr int kColParts = 64;       // row chunks of the column sums
 
-static SurWs carve(int64_t n, void *base) {
-    SurWs w{};
+// Workspace of a training step of n rows (a multiple of 256).
+static TrainBufs carve_train(int64_t n, void *base) {
+    TrainBufs w{};
     char *p = static_cast<char *>(base);
     size_t o = 0;
     auto take = [&](size_t bytes) { char *q = p ? p + o : nullptr; o = up256(o + bytes); return q; };
-    const size_t W = GTMP_SUR_WIDTH;
+    const size_t act = sizeof(uint16_t) * n * GTMP_SUR_WIDTH, slabs = (size_t)n / kTR;
+    w.Wf = reinterpret_cast<uint4 *>(take(sizeof(uint4) * kFragTotal));
+    w.Wb = reinterpret_cast<uint4 *>(take(sizeof(uint4) * 3 * kBackLayer));
     w.X0 = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * GTMP_SUR_IN));
-    for (int l = 0; l < 4; ++l) w.A[l] = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * W));
-    w.dZa = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * W));
-    w.dZb = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * W));
-    w.T1 = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * W));
-    w.T2 = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * W));
-    w.WT = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * W * W));
-    const size_t part_floats = std::max((size_t)kSplitsMax * W * W, (size_t)kColParts * W);
-    w.part = reinterpret_cast<float *>(take(sizeof(float) * part_floats));
-    w.loss_terms = reinterpret_cast<float *>(take(sizeof(float) * n));
-    w.dz = reinterpret_cast<float *>(take(sizeof(float) * n));
-    w.logit_tmp = reinterpret_cast<float *>(take(sizeof(float) * n));
-    w.Xf = reinterpret_cast<float *>(take(sizeof(float) * n * GTMP_MAX_DOF));
+    for (int l = 0; l < 3; ++l) w.A[l] = reinterpret_cast<uint16_t *>(take(act));
+    for (int l = 0; l < 4; ++l) w.dZ[l] = reinterpret_cast<uint16_t *>(take(act));
+    w.col = reinterpret_cast<float *>(take(sizeof(float) * 2 * slabs * kTVec * GTMP_SUR_WIDTH));
+    w.row = reinterpret_cast<float *>(take(sizeof(float) * 2 * slabs));
+    w.part = reinterpret_cast<float *>(take(sizeof(float) * kTSplit * kTWeights));
     w.total = o;
     return w;
 }
@@ -841,7 +1027,7 @@ static SurWs carve_infer(int64_t n, void *base) {
     return w;
 }
 
-size_t sur_workspace_bytes(int64_t n) { return carve(n, nullptr).total; }
+size_t sur_workspace_bytes(int64_t n) { return carve_train(n, nullptr).total; }
 
 int64_t sur_rows_for(size_t bytes) {
     // largest multiple of 256 rows whose inference carve-up fits
@@ -855,23 +1041,6 @@ int64_t sur_rows_for(size_t bytes) {
 }
 
 size_t sur_infer_bytes(int64_t n) { return carve_infer(n, nullptr).total; }
-
-// forward of rows [0, n) of X (FP32 [n][d]) into logits; activations kept in ws
-static void forward(const SurNet &net, int64_t n, const float *X, const SurWs &w, float *logits, const uint8_t *y,
-                    float inv_n, hipStream_t s) {
-    const SurLayout L = sur_layout();
-    hipLaunchKernelGGL(k_features, dim3(blocks_for(n)), dim3(256), 0, s, net.d, n, X, net.fourier, w.X0);
-    const uint16_t *in = w.X0;
-    int K = GTMP_SUR_IN;
-    for (int l = 0; l < 4; ++l) {
-        gemm<EPI_BIAS_RELU_BF16>((int)n, GTMP_SUR_WIDTH, K, 1, in, K, net.p16 + L.W[l], K, w.A[l], GTMP_SUR_WIDTH,
-                                 net.p32 + L.b[l], nullptr, 0, s);
-        in = w.A[l];
-        K = GTMP_SUR_WIDTH;
-    }
-    hipLaunchKernelGGL(k_head, dim3(blocks_for(n, 4)), dim3(256), 0, s, n, w.A[3], net.p16 + L.w5, net.p32 + L.b5, y,
-                       inv_n, logits, w.loss_terms, w.dz);
-}
 
 static void weight_frag(const SurNet &net, uint4 *Wf, hipStream_t s) {
     hipLaunchKernelGGL(k_weight_frag, dim3((kFragTotal + 255) / 256), dim3(256), 0, s, net.d, net.p16, sur_layout(),
@@ -898,52 +1067,17 @@ hipError_t launch_sur_infer(const SurNet &net, int64_t n, const float *X, float 
 hipError_t launch_sur_grad(const SurNet &net, int n, const float *X, const uint8_t *y, float *grad, float *loss,
                            float *logits, void *ws, hipStream_t s) {
     const SurLayout L = sur_layout();
-    const SurWs w = carve(n, ws);
-    const int W = GTMP_SUR_WIDTH;
-    forward(net, n, X, w, logits ? logits : w.logit_tmp, y, 1.f / (float)n, s);
-    // loss = mean of the per-row terms (fixed-order sums)
-    {
-        const int rpp = (n + kColParts - 1) / kColParts;
-        hipLaunchKernelGGL(k_colsum_part<float>, dim3(1, kColParts), dim3(256), 0, s, (int64_t)n, 1, rpp,
-                           w.loss_terms, (const float *)nullptr, w.part);
-        hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, kColParts, (int64_t)1, w.part, loss,
-                           1.f / (float)n);
-    }
-    // output layer: dW5 = sum_b dz a4, db5 = sum_b dz
-    const int rpp = (n + kColParts - 1) / kColParts;
-    hipLaunchKernelGGL(k_colsum_part<uint16_t>, dim3(1, kColParts), dim3(256), 0, s, (int64_t)n, W, rpp, w.A[3],
-                       w.dz, w.part);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, kColParts, (int64_t)W, w.part, grad + L.w5, 1.f);
-    hipLaunchKernelGGL(k_colsum_part<float>, dim3(1, kColParts), dim3(256), 0, s, (int64_t)n, 1, rpp, w.dz,
-                       (const float *)nullptr, w.part);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, kColParts, (int64_t)1, w.part, grad + L.b5, 1.f);
-    // dZ4
-    uint16_t *dZ = w.dZa, *dZn = w.dZb;
-    hipLaunchKernelGGL(k_head_back, dim3(blocks_for((int64_t)n * W)), dim3(256), 0, s, (int64_t)n, w.dz,
-                       net.p16 + L.w5, w.A[3], dZ);
-    int splits = 1;
-    while (splits < kSplitsMax && n / (splits * 2) >= 256 && (n % (splits * 2 * kBK)) == 0) splits *= 2;
-    for (int l = 3; l >= 0; --l) {
-        const int K_in = l == 0 ? GTMP_SUR_IN : W;
-        const uint16_t *A_prev = l == 0 ? w.X0 : w.A[l - 1];
-        // dW_l = dZ^T A_prev: transposes put the batch dimension last
-        hipLaunchKernelGGL(k_transpose_bf16, dim3(W / 64, n / 64), dim3(256), 0, s, n, W, dZ, w.T1);
-        hipLaunchKernelGGL(k_transpose_bf16, dim3(K_in / 64, n / 64), dim3(256), 0, s, n, K_in, A_prev, w.T2);
-        gemm<EPI_F32>(W, K_in, n, splits, w.T1, n, w.T2, n, w.part, K_in, nullptr, nullptr, 0, s);
-        hipLaunchKernelGGL(k_sum_parts, dim3(blocks_for((int64_t)W * K_in)), dim3(256), 0, s, splits,
-                           (int64_t)W * K_in, w.part, grad + L.W[l], 1.f);
-        // db_l = column sums of dZ (after the split-K partials are consumed)
-        hipLaunchKernelGGL(k_colsum_part<uint16_t>, dim3(1, kColParts), dim3(256), 0, s, (int64_t)n, W, rpp, dZ,
-                           (const float *)nullptr, w.part);
-        hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, kColParts, (int64_t)W, w.part, grad + L.b[l], 1.f);
-        if (l > 0) {
-            // dZ_{l-1} = bf16((dZ_l W_l) * [a_{l-1} > 0]): B operand W_l^T [K_in][W]
-            hipLaunchKernelGGL(k_transpose_bf16, dim3(K_in / 64, W / 64), dim3(256), 0, s, W, K_in,
-                               net.p16 + L.W[l], w.WT);
-            gemm<EPI_MASK_BF16>(n, K_in, W, 1, dZ, W, w.WT, W, dZn, K_in, nullptr, A_prev, K_in, s);
-            std::swap(dZ, dZn);
-        }
-    }
+    const TrainBufs w = carve_train(n, ws);
+    const int slabs = n / kTR;  // a multiple of kTSplit
+    static_assert(256 % (kTR * kTSplit) == 0, "every split takes whole slabs");
+    const float inv_n = 1.f / (float)n;
+    hipLaunchKernelGGL(k_train_frag, dim3(blocks_for(kFragTotal + 3 * kBackLayer)), dim3(256), 0, s, net.p16, L, w.Wf,
+                       w.Wb);
+    hipLaunchKernelGGL(k_train_rows, dim3((unsigned)slabs), dim3(512), 0, s, net.d, X, y, net.fourier, net.p16, net.p32,
+                       L, inv_n, logits, w);
+    hipLaunchKernelGGL(k_train_weights, dim3(kTSplit * kTTiles), dim3(256), 0, s, slabs / kTSplit, w);
+    hipLaunchKernelGGL(k_train_sums, dim3(kTSumWeights + kTSumCols + 1), dim3(256), 0, s, slabs, L, inv_n, w, grad,
+                       loss);
     return hipGetLastError();
 }
 
