@@ -12,14 +12,24 @@
 // between fields (SWAR addition).  The crossing decision is taken in FP32
 // with a fixed operation order; this file is compiled without contraction.
 //
-// Sweep: one wave per vertex u.  Lane j holds entry j of u's list (label, least
-// cost of a chain from u to the goal with that label, successor).  For every
-// successor v (in index order) the candidates kappa(u, v) + chi, C(u, v) +
-// J(v, chi) arrive one per lane (v's entries); each is matched against u's
-// entries by broadcast, a lower cost replaces the entry's, a new label is
-// appended.  When a list is full, a new label replaces the costliest entry if
-// it is cheaper and the overflow counter counts every label dropped: results
-// are exact whenever the counter stays zero.
+// Sweep: the list of a vertex u is what this sequential rule makes: for every
+// successor v in index order the candidates kappa(u, v) + chi, C(u, v) +
+// J(v, chi) are matched against u's entries, a lower cost replaces the entry's,
+// a new label is appended in candidate order; when the list is full, a new
+// label replaces the costliest entry if it is cheaper and the overflow counter
+// counts every label dropped: results are exact whenever the counter stays
+// zero.
+// While a list is not full, the rule only keeps labels in order of first
+// appearance with the first least cost, so runs of successors can be taken
+// side by side and joined in order: a block of eight waves per vertex, a run
+// of successors each, lane j of a wave holding entry j of its list, joined
+// pairwise in three steps.  A list that would overflow anywhere is built again
+// by one wave over all successors, by the rule itself.  A walk is a chain of
+// memory round trips, so a wave loads the edges of up to 64 successors at once
+// (their labels formed a successor per lane) and the next candidate list ahead.
+// A layer of M 4, N 128 with 15 class points takes 21 us on average (one wave
+// per vertex, one successor at a time: 130 us); what remains is the start
+// vertex's list where it overflows (55-80 us).
 #include "gtmp_launch.hpp"
 
 namespace gtmp {
@@ -44,20 +54,34 @@ __device__ __forceinline__ bool label_eq(const Label &a, const Label &b) {
     return a.w[0] == b.w[0] && a.w[1] == b.w[1];
 }
 
-// Signed crossings of u -> v with the upward rays of reps[0..k), packed in
+// The class points in LDS (a read of memory per point inside the walk waited
+// for memory k times); points past k are not looked at.
+struct Reps {
+    float x[kClassMaxReps], y[kClassMaxReps];
+};
+
+__device__ __forceinline__ uint32_t label_hash(const Label &a) {
+    return (uint32_t)a.w[0] * 0x9E3779B1u ^ (uint32_t)(a.w[0] >> 32) * 0x85EBCA77u ^ (uint32_t)a.w[1] * 0xC2B2AE3Du ^
+           (uint32_t)(a.w[1] >> 32) * 0x27D4EB2Fu;
+}
+
+// Signed crossings of u -> v with the upward rays of the k points, packed in
 // two's complement.
-__device__ __forceinline__ Label edge_label(float ux, float uy, float vx, float vy, const float *reps, int k) {
+__device__ __forceinline__ Label edge_label(float ux, float uy, float vx, float vy, const Reps &Z, int k) {
     Label lab{{0ull, 0ull}};
-    for (int i = 0; i < k; ++i) {
-        const float zx = reps[2 * i], zy = reps[2 * i + 1];
-        if ((ux < zx) == (vx < zx)) continue;
-        const float dx = vx - ux, dy = vy - uy, ex = zx - ux, ey = zy - uy;
+    const float dx = vx - ux, dy = vy - uy;
+    const uint32_t field = dx > 0.f ? 1u : 255u;  // +1 or -1 mod 256
+    uint32_t w[kClassMaxReps / 4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < kClassMaxReps; ++i) {
+        const float ex = Z.x[i] - ux, ey = Z.y[i] - uy;
         const float cross = dx * ey - dy * ex;
         const bool above = dx > 0.f ? cross < 0.f : cross > 0.f;
-        if (!above) continue;
-        const uint64_t field = dx > 0.f ? 1ull : 255ull;  // +1 or -1 mod 256
-        lab.w[i >> 3] |= field << (8 * (i & 7));
+        const bool on = i < k && (ux < Z.x[i]) != (vx < Z.x[i]) && above;
+        w[i >> 2] |= on ? field << (8 * (i & 3)) : 0u;
     }
+    lab.w[0] = (uint64_t)w[1] << 32 | w[0];
+    lab.w[1] = (uint64_t)w[3] << 32 | w[2];
     return lab;
 }
 
@@ -98,152 +122,254 @@ struct ClassLists {
     uint32_t *overflow;  // [1] labels dropped by full lists
 };
 
-// One wave per vertex u of layer m (m = -1: the start vertex).
-__global__ void __launch_bounds__(256) k_class_layer(int m, int M, int N, int G, int L, const float *__restrict__ Q,
-                                                     const float *__restrict__ q0, const float *__restrict__ goals,
-                                                     const float *__restrict__ C_s, const float *__restrict__ C_h,
-                                                     const float *__restrict__ C_l, float penalty,
-                                                     const float *__restrict__ reps, int k, ClassLists CL) {
-    const int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kWave);
+// A list: lane j holds entry j.
+struct ClassList {
+    Label lab;
+    float cost;
+    uint32_t nxt;
+    int cnt;
+    uint32_t dropped;
+};
+
+// The costliest of the list's entries (the highest lane among equals).
+__device__ __forceinline__ int costliest(const ClassList &U, float &mx) {
+    mx = lane_id() < U.cnt ? U.cost : -__builtin_inff();
+#define GTMP_DPP_MAX(ctrl, rows)                                                                                  \
+    mx = __builtin_fmaxf(mx, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(mx), __float_as_int(mx), ctrl, \
+                                                                        rows, 0xf, false)));
+    GTMP_DPP_MAX(0x111, 0xf)  // row_shr:1
+    GTMP_DPP_MAX(0x112, 0xf)  // row_shr:2
+    GTMP_DPP_MAX(0x114, 0xf)  // row_shr:4
+    GTMP_DPP_MAX(0x118, 0xf)  // row_shr:8
+    GTMP_DPP_MAX(0x142, 0xa)  // row_bcast:15 into rows 1 and 3
+    GTMP_DPP_MAX(0x143, 0xc)  // row_bcast:31 into rows 2 and 3
+#undef GTMP_DPP_MAX
+    mx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), kWave - 1));
+    return kWave - 1 - __builtin_clzll(ballot(lane_id() < U.cnt && U.cost == mx));
+}
+
+// The candidates of one successor (or list), one per lane, labels distinct,
+// into U.  EXACT: a full list follows the replacement rule; otherwise false is
+// returned and U is left as it was when the new labels do not fit.
+template <bool EXACT>
+__device__ __forceinline__ bool absorb(ClassList &U, int L, const Label &cl, float cc, uint32_t cn, int n_src) {
     const int lane = lane_id();
-    const int n_u = m < 0 ? 1 : N;
-    if (wave >= n_u) return;
-    const int u = wave;
-    const float *pu = m < 0 ? q0 : Q + ((size_t)m * N + u) * 2;
-    const float ux = pu[0], uy = pu[1];
-    const int nv = m == M - 1 ? G : N;
-
-    Label my_lab{{0ull, 0ull}};
-    float my_cost = __builtin_inff();
-    uint32_t my_nxt = 0;
-    int cnt = 0;
-    uint32_t dropped = 0;
-
-    for (int v = 0; v < nv; ++v) {
-        float c;
-        const float *pv;
-        if (m < 0) {
-            c = C_s[v];
-            pv = Q + (size_t)v * 2;
-        } else if (m == M - 1) {
-            c = C_l[(size_t)u * G + v];
-            pv = goals + (size_t)v * 2;
-        } else {
-            c = C_h[((size_t)m * N + u) * N + v];
-            pv = Q + ((size_t)(m + 1) * N + v) * 2;
-        }
-        c = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(c)));  // one value for the wave
-        if (!(c < penalty)) continue;  // absent or failed edge
-        const Label kap = edge_label(ux, uy, pv[0], pv[1], reps, k);
-        // candidates: one per lane
-        int n_src;
-        Label cl{{0ull, 0ull}};
-        float cc = __builtin_inff();
-        uint32_t cn = 0;
-        if (m == M - 1) {
-            n_src = 1;
-            if (lane == 0) {
-                cl = label_add(kap, Label{{kEmptyWord, kEmptyWord}});
-                cc = c;
-                cn = (uint32_t)v << 8;
-            }
-        } else {
-            const int mm = m + 1;  // successor layer (0 for the start)
-            n_src = __builtin_amdgcn_readfirstlane(CL.cnt[(size_t)mm * N + v]);
-            if (lane < n_src) {
-                const size_t base = ((size_t)mm * N + v) * L + lane;
-                cl = label_add(kap, load_label(CL.lab, base));
-                cc = c + CL.cost[base];
-                cn = ((uint32_t)v << 8) | (uint32_t)lane;
-            }
-        }
-        if (n_src == 0) continue;
-        // match: list lane j finds the candidate with its label (labels are
-        // distinct within u's list and within one successor's candidates)
-        uint64_t matched = 0;
-        int src = -1;
+    // match: list lane j finds the candidate with its label (labels are
+    // distinct within both), by broadcasting the fewer of candidates and
+    // entries as 32-bit hashes; a pair that only the hash takes for equal shows
+    // in the whole labels compared afterwards or in the number of pairs, and
+    // the labels themselves are then broadcast
+    uint64_t matched = 0;
+    int src = -1;
+    const uint32_t hu = label_hash(U.lab), hc = label_hash(cl);
+    if (n_src <= U.cnt) {
         for (int e = 0; e < n_src; ++e) {
-            const Label le = readlane_label(cl, e);
-            const bool hit = lane < cnt && label_eq(my_lab, le);
-            if (hit) src = e;
-            if (ballot(hit) != 0) matched |= 1ull << e;
+            const bool hit = lane < U.cnt && hu == (uint32_t)__builtin_amdgcn_readlane((int)hc, e);
+            src = hit ? e : src;
+            matched |= ballot(hit) != 0 ? 1ull << e : 0ull;
         }
-        {
-            const float pc = __shfl(cc, src < 0 ? 0 : src);
-            const uint32_t pn = (uint32_t)__shfl((int)cn, src < 0 ? 0 : src);
-            if (src >= 0 && pc < my_cost) {
-                my_cost = pc;
-                my_nxt = pn;
+    } else {
+        for (int j = 0; j < U.cnt; ++j) {
+            const uint64_t hit = ballot(lane < n_src && hc == (uint32_t)__builtin_amdgcn_readlane((int)hu, j));
+            src = lane == j && hit != 0 ? __builtin_ctzll(hit) : src;
+            matched |= hit;
+        }
+    }
+    if (matched != 0) {
+        const int from = src < 0 ? 0 : src;
+        const Label l{{shfl64(cl.w[0], from), shfl64(cl.w[1], from)}};
+        const bool wrong = src >= 0 && !label_eq(l, U.lab);
+        if (ballot(wrong) != 0 || __popcll(matched) != __popcll(ballot(src >= 0))) {
+            matched = 0;
+            src = -1;
+            for (int e = 0; e < n_src; ++e) {
+                const bool hit = lane < U.cnt && label_eq(U.lab, readlane_label(cl, e));
+                if (hit) src = e;
+                if (ballot(hit) != 0) matched |= 1ull << e;
             }
         }
-        // new labels: appended in candidate order while there is room
-        uint64_t pending = (n_src >= 64 ? ~0ull : ((1ull << n_src) - 1ull)) & ~matched;
-        const int n_new = __popcll(pending);
-        if (n_new == 0) continue;
-        const int room = L - cnt;
-        const int n_app = n_new < room ? n_new : room;
+    }
+    uint64_t pending = (n_src >= 64 ? ~0ull : ((1ull << n_src) - 1ull)) & ~matched;
+    const int n_new = __popcll(pending), room = L - U.cnt;
+    if (!EXACT && n_new > room) return false;
+    if (matched != 0) {
+        const float pc = __shfl(cc, src < 0 ? 0 : src);
+        const uint32_t pn = (uint32_t)__shfl((int)cn, src < 0 ? 0 : src);
+        if (src >= 0 && pc < U.cost) {
+            U.cost = pc;
+            U.nxt = pn;
+        }
+    }
+    if (n_new == 0) return true;
+    // new labels: appended in candidate order while there is room
+    const int n_app = n_new < room ? n_new : room;
+    if (n_app > 0) {
         int asrc = -1;
         for (int idx = 0; idx < n_app; ++idx) {
             const int e = __builtin_ctzll(pending);
             pending &= pending - 1;
-            if (lane == cnt + idx) asrc = e;
+            if (lane == U.cnt + idx) asrc = e;
         }
-        {
-            const int from = asrc < 0 ? 0 : asrc;
-            const Label pl{{shfl64(cl.w[0], from), shfl64(cl.w[1], from)}};
-            const float pc = __shfl(cc, from);
-            const uint32_t pn = (uint32_t)__shfl((int)cn, from);
-            if (asrc >= 0) {
-                my_lab = pl;
-                my_cost = pc;
-                my_nxt = pn;
-            }
+        const int from = asrc < 0 ? 0 : asrc;
+        const Label pl{{shfl64(cl.w[0], from), shfl64(cl.w[1], from)}};
+        const float pc = __shfl(cc, from);
+        const uint32_t pn = (uint32_t)__shfl((int)cn, from);
+        if (asrc >= 0) {
+            U.lab = pl;
+            U.cost = pc;
+            U.nxt = pn;
         }
-        cnt += n_app;
-        // full list: each remaining label replaces the costliest entry if cheaper
+        U.cnt += n_app;
+    }
+    if constexpr (EXACT) {
+        // full list: each remaining label replaces the costliest entry if
+        // cheaper; that entry's cost never rises, so a candidate that is not
+        // cheaper now is not later either
+        U.dropped += (uint32_t)__popcll(pending);  // either the label or the one it replaces
         while (pending != 0) {
+            float mx;
+            const int arg = costliest(U, mx);
+            pending &= ballot(cc < mx);
+            if (pending == 0) break;
             const int e = __builtin_ctzll(pending);
             pending &= pending - 1;
             const Label el = readlane_label(cl, e);
             const float ec = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cc), e));
             const uint32_t en = __builtin_amdgcn_readlane(cn, e);
-            float mx = lane < cnt ? my_cost : -__builtin_inff();
-            int arg = lane;
-#pragma unroll
-            for (int off = kWave / 2; off > 0; off >>= 1) {
-                const float om = __shfl_xor(mx, off);
-                const int oa = __shfl_xor(arg, off);
-                if (om > mx || (om == mx && oa > arg)) {
-                    mx = om;
-                    arg = oa;
-                }
-            }
-            ++dropped;  // either this label or the replaced one
-            if (ec < mx && lane == arg) {
-                my_lab = el;
-                my_cost = ec;
-                my_nxt = en;
+            if (lane == arg) {
+                U.lab = el;
+                U.cost = ec;
+                U.nxt = en;
             }
         }
+    }
+    return true;
+}
+
+struct ClassArgs {
+    int m, M, N, G, L, k;
+    const float *Q, *q0, *goals, *C_s, *C_h, *C_l, *reps;
+    float penalty;
+};
+
+// Successors [v0, v1) of vertex u into U in index order; false when a list
+// that is not EXACT overflows.
+template <bool EXACT>
+__device__ __forceinline__ bool walk(const ClassArgs &A, const ClassLists &CL, int u, int v0, int v1,
+                                     const Reps &Z, ClassList &U) {
+    const int lane = lane_id(), m = A.m, N = A.N, L = A.L;
+    const bool last = m == A.M - 1;
+    const float *pu = m < 0 ? A.q0 : A.Q + ((size_t)m * N + u) * 2;
+    const float *row = m < 0 ? A.C_s : last ? A.C_l + (size_t)u * A.G : A.C_h + ((size_t)m * N + u) * N;
+    const float *succ = last ? A.goals : A.Q + (size_t)(m + 1) * N * 2;  // layer 0 for the start
+    const size_t first = (size_t)(m + 1) * N;
+    const float ux = pu[0], uy = pu[1];
+    for (int base = v0; base < v1; base += kWave) {
+        const int v = base + lane;
+        float c = __builtin_inff();
+        int ns = 0;
+        Label kap{{0ull, 0ull}};
+        if (v < v1) {
+            c = row[v];
+            ns = last ? 1 : CL.cnt[first + v];
+            kap = edge_label(ux, uy, succ[2 * v], succ[2 * v + 1], Z, A.k);
+        }
+        uint64_t live = ballot(c < A.penalty && ns > 0);  // absent and failed edges are skipped
+        // the next successor's candidates are requested before this one's are absorbed
+        int b = 0, n = 0;
+        Label cl{{kEmptyWord, kEmptyWord}};
+        float cc = 0.f;
+        auto next = [&]() {
+            n = 0;
+            if (live == 0) return;
+            b = __builtin_ctzll(live);
+            live &= live - 1;
+            n = __builtin_amdgcn_readlane(ns, b);
+            if (!last && lane < n) {
+                const size_t at = (first + base + b) * L + lane;
+                cl = load_label(CL.lab, at);
+                cc = CL.cost[at];
+            }
+        };
+        next();
+        while (n != 0) {
+            const float ce = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c), b));
+            const Label l = label_add(readlane_label(kap, b), cl);
+            const float cost = last ? ce : ce + cc;
+            const uint32_t cn = ((uint32_t)(base + b) << 8) | (last ? 0u : (uint32_t)lane);
+            const int ne = n;
+            next();
+            if (!absorb<EXACT>(U, L, l, cost, cn, ne)) return false;
+        }
+    }
+    return true;
+}
+
+constexpr int kClassWaves = 8;  // waves (runs of successors) per vertex
+
+// A block per vertex u of layer A.m (-1: the start vertex).
+__global__ void __launch_bounds__(kClassWaves *kWave) k_class_layer(ClassArgs A, ClassLists CL) {
+    __shared__ Label lab_s[kClassWaves][kWave];
+    __shared__ float cost_s[kClassWaves][kWave];
+    __shared__ uint32_t nxt_s[kClassWaves][kWave];
+    __shared__ int cnt_s[kClassWaves], over_s;
+    const int u = blockIdx.x, lane = lane_id(), w = (int)wave_in_block();
+    const int nv = A.m == A.M - 1 ? A.G : A.N;
+    const int per = (nv + kClassWaves - 1) / kClassWaves;
+    ClassList U{Label{{0ull, 0ull}}, __builtin_inff(), 0u, 0, 0u};
+    __shared__ Reps Z;
+    if ((int)threadIdx.x < kClassMaxReps) {
+        const int i = threadIdx.x;
+        Z.x[i] = i < A.k ? A.reps[2 * i] : 0.f;
+        Z.y[i] = i < A.k ? A.reps[2 * i + 1] : 0.f;
+    }
+    if (threadIdx.x == 0) over_s = 0;
+    __syncthreads();
+    {
+        const int v0 = w * per < nv ? w * per : nv, v1 = v0 + per < nv ? v0 + per : nv;
+        if (!walk<false>(A, CL, u, v0, v1, Z, U) && lane == 0) over_s = 1;
+    }
+    auto publish = [&]() {
+        lab_s[w][lane] = U.lab;
+        cost_s[w][lane] = U.cost;
+        nxt_s[w][lane] = U.nxt;
+        if (lane == 0) cnt_s[w] = U.cnt;
+    };
+#pragma unroll
+    for (int step = 1; step < kClassWaves; step <<= 1) {  // list w takes list w + step
+        if ((w & (2 * step - 1)) == step) publish();
+        __syncthreads();
+        if ((w & (2 * step - 1)) == 0) {
+            const int o = w + step, n = cnt_s[o];
+            if (n > 0 && over_s == 0 && !absorb<false>(U, A.L, lab_s[o][lane], cost_s[o][lane], nxt_s[o][lane], n) &&
+                lane == 0)
+                over_s = 1;
+        }
+        __syncthreads();
+    }
+    if (w != 0) return;
+    if (over_s != 0) {
+        U = ClassList{Label{{0ull, 0ull}}, __builtin_inff(), 0u, 0, 0u};
+        walk<true>(A, CL, u, 0, nv, Z, U);
     }
     // store u's list
-    if (m < 0) {
-        if (lane < cnt) {
-            store_label(CL.s_lab, lane, my_lab);
-            CL.s_cost[lane] = my_cost;
-            CL.s_nxt[lane] = my_nxt;
+    if (A.m < 0) {
+        if (lane < U.cnt) {
+            store_label(CL.s_lab, lane, U.lab);
+            CL.s_cost[lane] = U.cost;
+            CL.s_nxt[lane] = U.nxt;
         }
-        if (lane == 0) *CL.s_cnt = cnt;
+        if (lane == 0) *CL.s_cnt = U.cnt;
     } else {
-        const size_t base = ((size_t)m * N + u) * L;
-        if (lane < cnt) {
-            store_label(CL.lab, base + lane, my_lab);
-            CL.cost[base + lane] = my_cost;
-            CL.nxt[base + lane] = my_nxt;
+        const size_t base = ((size_t)A.m * A.N + u) * A.L;
+        if (lane < U.cnt) {
+            store_label(CL.lab, base + lane, U.lab);
+            CL.cost[base + lane] = U.cost;
+            CL.nxt[base + lane] = U.nxt;
         }
-        if (lane == 0) CL.cnt[(size_t)m * N + u] = cnt;
+        if (lane == 0) CL.cnt[(size_t)A.m * A.N + u] = U.cnt;
     }
-    if (lane == 0 && dropped) atomicAdd(CL.overflow, dropped);
+    if (lane == 0 && U.dropped) atomicAdd(CL.overflow, U.dropped);
 }
 
 // Chains of the start list: lane e follows entry e through the layers.
@@ -269,46 +395,64 @@ __global__ void k_class_reset(uint32_t *overflow) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *overflow = 0u;
 }
 
-// Class-indexed archive update (one wave): per label the lowest cost, a later
+// Class-indexed archive update (one block): per label the lowest cost, a later
 // stage replacing an entry only with a strictly lower cost; waypoints copied
-// from this stage's samples.
-__global__ void __launch_bounds__(64) k_class_archive(int M, int N, int stage, const float *__restrict__ Q,
-                                                      const float *__restrict__ q0, const float *__restrict__ goals,
-                                                      const uint64_t *labels, const float *costs,
-                                                      const int32_t *chains, const int32_t *count, int cap,
-                                                      uint64_t *a_lab, float *a_cost, int32_t *a_stage, float *a_wp,
-                                                      int32_t *a_count, uint32_t *overflow) {
-    const int lane = lane_id();
-    const int n = *count;
-    // the labels of one stage are distinct, so only entries of earlier stages
-    // (the first na0) can match; new entries are appended after them
+// from this stage's samples.  The labels of one stage are distinct, so only
+// entries of earlier stages (the first na0) can match: the classes are looked
+// up side by side, a wave each, the new ones then take slots in class order
+// (one wave taking the classes in turn: 33 us a stage against 6.5).
+constexpr int kArchiveThreads = 1024;
+
+__global__ void __launch_bounds__(kArchiveThreads) k_class_archive(int M, int N, int stage, const float *__restrict__ Q,
+                                                                   const float *__restrict__ q0,
+                                                                   const float *__restrict__ goals,
+                                                                   const uint64_t *labels, const float *costs,
+                                                                   const int32_t *chains, const int32_t *count, int cap,
+                                                                   uint64_t *a_lab, float *a_cost, int32_t *a_stage,
+                                                                   float *a_wp, int32_t *a_count, uint32_t *overflow) {
+    __shared__ int slot_s[kWave];  // per class: its archive slot, -1 new, -2 none
+    const int lane = lane_id(), w = (int)wave_in_block();
+    constexpr int kWaves = kArchiveThreads / kWave;
+    const int n = *count;  // at most kWave
     const int na0 = *a_count;
-    int na = na0;
-    for (int e = 0; e < n; ++e) {
-        const uint64_t lab0 = labels[2 * e], lab1 = labels[2 * e + 1];
-        const float c = costs[e];
+    for (int e = w; e < n; e += kWaves) {
+        const Label lab{{labels[2 * e], labels[2 * e + 1]}};
         int found = -1;
-        for (int base = 0; base < na0; base += kWave) {
-            const int j = base + lane;
-            const uint64_t hit = ballot(j < na0 && a_lab[2 * j] == lab0 && a_lab[2 * j + 1] == lab1);
-            if (hit != 0) {
-                found = base + __builtin_ctzll(hit);
-                break;
+        for (int base = 0; base < na0 && found < 0; base += 4 * kWave) {
+            bool hit[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j = base + q * kWave + lane;
+                hit[q] = j < na0 && a_lab[2 * j] == lab.w[0] && a_lab[2 * j + 1] == lab.w[1];
+            }
+#pragma unroll
+            for (int q = 3; q >= 0; --q) {
+                const uint64_t b = ballot(hit[q]);
+                if (b != 0) found = base + q * kWave + __builtin_ctzll(b);
             }
         }
-        int slot = -1;
-        if (found >= 0) {
-            if (c < a_cost[found]) slot = found;
-        } else if (na < cap) {
-            slot = na++;
-        } else if (lane == 0) {
-            atomicAdd(overflow, 1u);
+        if (lane == 0) slot_s[e] = found < 0 ? -1 : costs[e] < a_cost[found] ? found : -2;
+    }
+    __syncthreads();
+    if (w == 0) {
+        const bool fresh = lane < n && slot_s[lane] == -1;
+        const uint64_t b = ballot(fresh);
+        const int s = na0 + rank_in(b), total = __popcll(b);
+        if (fresh) slot_s[lane] = s < cap ? s : -2;
+        const int room = cap - na0 < total ? cap - na0 : total;
+        if (lane == 0) {
+            *a_count = na0 + room;
+            if (total > room) atomicAdd(overflow, (uint32_t)(total - room));
         }
+    }
+    __syncthreads();
+    for (int e = w; e < n; e += kWaves) {
+        const int slot = slot_s[e];
         if (slot < 0) continue;
         if (lane == 0) {
-            a_lab[2 * slot] = lab0;
-            a_lab[2 * slot + 1] = lab1;
-            a_cost[slot] = c;
+            a_lab[2 * slot] = labels[2 * e];  // the caller's array: 8-byte words
+            a_lab[2 * slot + 1] = labels[2 * e + 1];
+            a_cost[slot] = costs[e];
             a_stage[slot] = stage;
         }
         // waypoints q0, Q[0][i0], ..., Q[M-1][i_{M-1}], goal
@@ -320,7 +464,6 @@ __global__ void __launch_bounds__(64) k_class_archive(int M, int N, int stage, c
             wp[2 * p + 1] = src[1];
         }
     }
-    if (lane == 0) *a_count = na;
 }
 
 // ------------------------------------------------------------------ host side
@@ -362,12 +505,9 @@ hipError_t launch_class_sweep(int M, int N, int G, int L, const float *Q, const 
     const ClassPlan p = make_class_plan(M, N, L);
     const ClassLists CL = carve_lists(p, L, ws, overflow);
     if (reset_overflow) hipLaunchKernelGGL(k_class_reset, dim3(1), dim3(64), 0, s, overflow);
-    const unsigned blocks = (unsigned)((N + 3) / 4);
-    for (int m = M - 1; m >= 0; --m)
-        hipLaunchKernelGGL(k_class_layer, dim3(blocks), dim3(256), 0, s, m, M, N, G, L, Q, q0, goals, C_s, C_h, C_l,
-                           penalty, reps, k, CL);
-    hipLaunchKernelGGL(k_class_layer, dim3(1), dim3(256), 0, s, -1, M, N, G, L, Q, q0, goals, C_s, C_h, C_l, penalty,
-                       reps, k, CL);
+    ClassArgs A{0, M, N, G, L, k, Q, q0, goals, C_s, C_h, C_l, reps, penalty};
+    for (A.m = M - 1; A.m >= -1; --A.m)
+        hipLaunchKernelGGL(k_class_layer, dim3(A.m < 0 ? 1u : (unsigned)N), dim3(kClassWaves * kWave), 0, s, A, CL);
     hipLaunchKernelGGL(k_class_extract, dim3(1), dim3(64), 0, s, M, N, L, CL, labels, costs, chains, count);
     return hipGetLastError();
 }
@@ -376,8 +516,8 @@ hipError_t launch_class_archive(int M, int N, int stage, const float *Q, const f
                                 const uint64_t *labels, const float *costs, const int32_t *chains,
                                 const int32_t *count, int cap, uint64_t *a_lab, float *a_cost, int32_t *a_stage,
                                 float *a_wp, int32_t *a_count, uint32_t *overflow, hipStream_t s) {
-    hipLaunchKernelGGL(k_class_archive, dim3(1), dim3(64), 0, s, M, N, stage, Q, q0, goals, labels, costs, chains,
-                       count, cap, a_lab, a_cost, a_stage, a_wp, a_count, overflow);
+    hipLaunchKernelGGL(k_class_archive, dim3(1), dim3(kArchiveThreads), 0, s, M, N, stage, Q, q0, goals, labels, costs,
+                       chains, count, cap, a_lab, a_cost, a_stage, a_wp, a_count, overflow);
     return hipGetLastError();
 }
 
