@@ -69,13 +69,21 @@ __global__ void __launch_bounds__(256) k_wave_stats_sum(const unsigned long long
 
 // The per-wave slots of a grid of grid_blocks blocks of 256 threads (NULL:
 // its waves add to the counters directly).
-static unsigned long long *wave_stat_slots(const EdgeArgs &A, unsigned grid_blocks) {
+// A lazy round's list kernels always take slots (one for each wave of the
+// larger grid): thousands of waves adding to the counters took 0.1 ms.
+static unsigned list_blocks();
+static unsigned long long *wave_stat_slots(EdgeArgs &A, unsigned grid_blocks) {
+    if (A.edge_list) {
+        const uint64_t w = (uint64_t)std::max(grid_blocks, list_blocks()) * (256 / kWave);
+        A.list_waves = (uint32_t)(w < kStatWaves ? w : kStatWaves);
+        return A.stats ? A.wstats : nullptr;
+    }
     return A.stats && (uint64_t)grid_blocks * (256 / kWave) >= kStatSlotsMinWaves ? A.wstats : nullptr;
 }
 
 static void finish_wave_stats(const EdgeArgs &A, unsigned grid_blocks, hipStream_t s) {
     if (!A.stats || !A.wstats) return;
-    const uint64_t all = (uint64_t)grid_blocks * (256 / kWave);
+    const uint64_t all = A.edge_list ? A.list_waves : (uint64_t)grid_blocks * (256 / kWave);
     const uint32_t waves = (uint32_t)(all < kStatWaves ? all : kStatWaves);
     hipLaunchKernelGGL(k_wave_stats_sum, dim3((waves + 255) / 256), dim3(256), 0, s, A.wstats, waves, A.stats);
 }
@@ -213,11 +221,6 @@ __global__ void __launch_bounds__(kWave) k_store_params_tol(ArmParams R, ArmPara
     store_params_tol_wave(R, dst, S);
 }
 
-__global__ void k_zero_u32(uint32_t *p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
 __global__ void __launch_bounds__(kGridBuildThreads) k_build_grid(SceneParams S, int wdim, float r_max,
                                                                         ObsGrid *G) {
     build_grid_block(S, wdim, r_max, G);
@@ -347,8 +350,15 @@ static inline unsigned prepass_blocks(const EdgeArgs &A) { return prepass_block_
 // Lazy lists of at most this many (edge, state) pairs are checked by
 // k_list_states, all states side by side; longer ones by the early-exit
 // interior kernel in list mode (both are launched; each returns at once when
-// the list is the other's).
-__device__ __forceinline__ uint64_t list_states_limit() { return 1ull << 19; }
+// the list is the other's).  Arms behind the bins: about half of a round's
+// edges are free and the others fail after three states, so walking them saves
+// 40 % of the states but chains up to H - 2 evaluations of some 12 us each
+// (40 k edges of 14 states: 206 us walking, 36 side by side); a chip full of
+// waves takes 2^22 pairs in about the time of that chain.
+template <class Model>
+__device__ __forceinline__ uint64_t list_states_limit() {
+    return Model::kArm && Model::kGrid ? 1ull << 22 : 1ull << 19;
+}
 
 // LIST: the edges of a lazy round's list (A.edge_list, *A.n_list of them)
 // when the list is too long for k_list_states to take all their states at
@@ -423,10 +433,7 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? 6 : 4) : NC
     uint32_t chunk = kWave;
     if constexpr (LIST) {
         const uint32_t n_list = uniform(*A.n_list);
-        if ((uint64_t)n_list * (uint32_t)A.n_int <= list_states_limit()) {  // k_list_states took it
-            if (A.stats && lane_id() == 0) store_wave_stats(A, 0, 0, 0);
-            return;
-        }
+        if ((uint64_t)n_list * (uint32_t)A.n_int <= list_states_limit<Model>()) return;  // k_list_states took it
         const uint32_t waves = gridDim.x * (blockDim.x / kWave);
         chunk = (n_list + waves - 1) / waves;
         chunk = chunk < (uint32_t)kListChunk ? (uint32_t)kListChunk : chunk > (uint32_t)kWave ? (uint32_t)kWave : chunk;
@@ -769,10 +776,10 @@ __global__ void __launch_bounds__(kTile) k_finalize_no_interior(EdgeArgs A) {
 // overlap.  A colliding state marks its edge (list_mark[e] = 2), and
 // k_list_finish then writes every listed edge's cost and flag as the full
 // check does.
-constexpr int kListBlocksPerCu = 4;
+constexpr int kListBlocksPerCu = 6;
 
 template <class Model, bool UNIFORM_R, int NCH>
-__global__ void __launch_bounds__(256, 3) k_list_states(EdgeArgs A, const ArmParams *Rg, SceneParams S) {
+__global__ void __launch_bounds__(256, Model::kArm && Model::kGrid ? 6 : 3) k_list_states(EdgeArgs A, const ArmParams *Rg, SceneParams S) {
     constexpr int D = Model::D;
     constexpr int KP = Model::KP;
     constexpr bool ARM = Model::kArm;
@@ -785,9 +792,7 @@ __global__ void __launch_bounds__(256, 3) k_list_states(EdgeArgs A, const ArmPar
     const ObsGrid &G = *reinterpret_cast<const ObsGrid *>(&glds_raw);
     for (int i = threadIdx.x; i < A.n_int; i += blockDim.x) tord[i] = A.tord[i];
     if constexpr (GRID) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(A.grid);
-        uint4 *dst = reinterpret_cast<uint4 *>(&glds_raw);
-        for (int i = threadIdx.x; i < (int)(grid_lds_bytes<WG>() / 16); i += blockDim.x) dst[i] = src[i];
+        copy_to_lds<grid_lds_bytes<WG>(), 256>(&glds_raw, A.grid, threadIdx.x);
     }
     __syncthreads();
     float ginv[3] = {0.f, 0.f, 0.f}, goff[3] = {0.f, 0.f, 0.f};
@@ -800,16 +805,25 @@ __global__ void __launch_bounds__(256, 3) k_list_states(EdgeArgs A, const ArmPar
     }
     const int lane = lane_id();
     const uint32_t n_int = (uint32_t)A.n_int;
-    const uint64_t n_items = (uint64_t)uniform(*A.n_list) * n_int;
-    if (n_items > list_states_limit()) return;  // long lists: the early-exit kernel takes them
-    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / kWave);
+    const uint32_t waves = gridDim.x * (blockDim.x / kWave);
+    if (blockIdx.x == 0) {
+        // for the early-exit kernel, which the stream orders after this one:
+        // its cursors, and the statistics slots of its waves past this grid's
+        for (int i = threadIdx.x; i < kCursors * kCursorStride; i += 256) A.counter[i] = 0u;
+        if (A.wstats)
+            for (uint32_t i = waves + threadIdx.x; i < A.list_waves; i += 256)
+                for (int c = 0; c < 3; ++c) A.wstats[4 * (size_t)i + c] = 0ull;
+    }
+    const uint64_t all = (uint64_t)uniform(*A.n_list) * n_int;
+    // long lists: the early-exit kernel takes them
+    const uint32_t n_items = all > list_states_limit<Model>() ? 0u : (uint32_t)all;
     unsigned long long n_states = 0;
     uint32_t n_tests = 0;
-    for (uint64_t base = ((uint64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) * kWave; base < n_items;
+    for (uint32_t base = (blockIdx.x * (blockDim.x / kWave) + wave_in_block()) * kWave; base < n_items;
          base += waves * kWave) {
-        const uint64_t item = base + (uint64_t)lane;
+        const uint32_t item = base + (uint32_t)lane;
         const bool live = item < n_items;
-        const uint32_t k = live ? (uint32_t)(item / n_int) : 0u, jj = live ? (uint32_t)(item - (uint64_t)k * n_int) : 0u;
+        const uint32_t k = live ? item / n_int : 0u, jj = live ? item - k * n_int : 0u;
         const uint32_t e = A.edge_list[k];
         uint32_t uid, vid;
         edge_vertex_ids(A, e, uid, vid);
@@ -825,8 +839,8 @@ __global__ void __launch_bounds__(256, 3) k_list_states(EdgeArgs A, const ArmPar
             asm volatile("" : "+s"(Rp));
             const auto &R = *Rp;
             if constexpr (GRID) {
-                hit = arm_hit_grid<Model::kWords>(R, q, G.mask, G.rec, ginv, goff, gque[wave_in_block()], n_tests,
-                                                   live);
+                hit = arm_hit_grid<Model::kWords, UNIFORM_R>(R, q, G.mask, G.rec, ginv, goff, gque[wave_in_block()],
+                                                             n_tests, live);
             } else {
                 const v32f o = arm_fk<D>(R, q);
                 hit = arm_state_gap<KP, NCH, UNIFORM_R>(R, o, R.r0, S) <= 0.f;
@@ -841,10 +855,7 @@ __global__ void __launch_bounds__(256, 3) k_list_states(EdgeArgs A, const ArmPar
         if (live && hit) A.list_mark[e] = 2;
         n_states += (unsigned long long)__popcll(ballot(live));
     }
-    if (A.stats && lane == 0) {
-        atomicAdd(&A.stats[0], n_states);
-        if constexpr (GRID) atomicAdd(&A.stats[2], (unsigned long long)n_tests);  // wave total
-    }
+    if (A.stats && lane == 0) store_wave_stats(A, n_states, 0, GRID ? n_tests : 0u);
 }
 
 // Costs and flags of the listed edges: length if no state collided, else
@@ -1053,18 +1064,18 @@ static hipError_t launch_arm_kp(const EdgeArgs &A, const ArmParams &R, const Sce
     }
     if (!(phases & kPhaseEdges)) return hipGetLastError();
     if (!A.edge_list) hipLaunchKernelGGL(k_prepass<GTMP_MAX_JOINTS>, dim3(prepass_blocks(A)), dim3(kTile), 0, s, A);
-    if (gw && A.n_int > 0 && !(phases & kPhaseVertices))  // an edge pass on its own: bins built afresh
-        hipLaunchKernelGGL(k_build_grid, dim3(1), dim3(kGridBuildThreads), 0, s, S, 3, r_max, grid);
+    // (an edge pass on its own follows a vertex pass on the same workspace: its
+    // bins and robot table are there)
     if (o.ev_begin) (void)hipEventRecord((hipEvent_t)o.ev_begin, s);
     if (A.edge_list) {  // lazy round: the listed edges, states side by side
         const unsigned lb = list_blocks();
         if (A.n_int > 0) {
             if (gw == 1) {
-                hipLaunchKernelGGL((k_list_states<ArmGridModel<1>, true, 1>), dim3(lb), dim3(256), 0, s, A, Rg, S);
+                hipLaunchKernelGGL((R.uniform_r ? k_list_states<ArmGridModel<1>, true, 1> : k_list_states<ArmGridModel<1>, false, 1>), dim3(lb), dim3(256), 0, s, A, Rg, S);
                 hipLaunchKernelGGL((k_interior<ArmGridModel<1>, true, 1, true>), dim3(grid_persist), dim3(256), 0, s, A,
                                    Rg, S);
             } else if (gw == 2) {
-                hipLaunchKernelGGL((k_list_states<ArmGridModel<2>, true, 1>), dim3(lb), dim3(256), 0, s, A, Rg, S);
+                hipLaunchKernelGGL((R.uniform_r ? k_list_states<ArmGridModel<2>, true, 1> : k_list_states<ArmGridModel<2>, false, 1>), dim3(lb), dim3(256), 0, s, A, Rg, S);
                 hipLaunchKernelGGL((k_interior<ArmGridModel<2>, true, 1, true>), dim3(grid_persist), dim3(256), 0, s, A,
                                    Rg, S);
             } else if (R.uniform_r) {
@@ -1266,12 +1277,9 @@ hipError_t launch_edge_phases(const EdgePlan &plan, const ArmParams *arm, const 
         return hipGetLastError();
     }
 
-    // fast mode: the tile cursors are reset by the pre-pass; a lazy round's
-    // list has no pre-pass and resets them with a fill kernel (no memset
-    // node, so the sequence can be captured into a graph and replayed)
-    if ((phases & kPhaseEdges) && A.edge_list)
-        hipLaunchKernelGGL(k_zero_u32, dim3(kCursors * kCursorStride / 256), dim3(256), 0, s, A.counter,
-                           kCursors * kCursorStride);
+    // fast mode: the tile cursors are reset by the pre-pass, or by the first of
+    // a lazy round's list kernels (no memset node, so the sequence can be
+    // captured into a graph and replayed)
     if (arm) {
         const int kp = round_kp(R.n_spheres);
         const int n_obs = scene.n_sph + scene.n_box;

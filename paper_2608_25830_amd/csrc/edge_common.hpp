@@ -104,6 +104,7 @@ struct EdgeArgs {
     const uint32_t *edge_list;  // lazy rounds: the edges to check (flat ids), *n_list of them
     const uint32_t *n_list;
     uint8_t *list_mark;         // lazy rounds: per flat edge id, set to 2 when a listed edge collides
+    uint32_t list_waves;        // lazy rounds: statistics slots of the list kernels
     unsigned long long *stats;
     unsigned long long *wstats;  // [kStatWaves][4]: the interior kernel's per-wave totals, or NULL: atomics
     const ObsGrid *grid;  // arms with the bin filter: the obstacle bins of this scene
