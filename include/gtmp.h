@@ -533,9 +533,10 @@ gtmp_status gtmp_batch_workspace_size(const gtmp_plan_desc *plans, int32_t n, co
  * after waiting for `stream`, then enqueues the stages, or with use_graph
  * captures them into a graph and launches it, asynchronously.  With use_graph
  * a later call with byte-identical plan descriptors, options, output
- * pointers and workspace only launches the kept graph (no host tables, no
- * wait), re-uploading the tables first (with the wait) if another batch used
- * that workspace in between.  At most 64 graphs are kept per process; past
+ * pointers and workspace only copies its tables into the workspace again
+ * (asynchronously, from pinned memory kept with the graph: the workspace may
+ * have been freed and reused since) and launches the kept graph, without
+ * building tables or waiting.  At most 64 graphs are kept per process; past
  * that a call captures, launches and waits for its graph, then releases it. */
 gtmp_status gtmp_plan_batch(const gtmp_plan_desc *plans, int32_t n, const gtmp_batch_opts *opts, float *best_cost,
                             int32_t *best_idx, float *best_wp, int32_t *best_meta, float *stage_costs,

@@ -5,6 +5,8 @@
 // (Alg. 1 gtmp / anytime-gtmp / ao-gtmp), and every result equals the
 // single-plan call with the same seed: the kernels run the same per-edge,
 // per-row and per-plan code as the single-plan ones.
+#include <string.h>
+
 #include <map>
 #include <mutex>
 #include <string>
@@ -681,11 +683,13 @@ BatchLayout make_batch_layout(const gtmp_plan_desc *plans, int n, const gtmp_bat
         }
     }
     L.max_stages = max_stages;
+    // the tables the host writes, together
     L.off_arm = off; off = up(off + sizeof(ArmParams) * (size_t)n);
-    L.off_grids = off; off = up(off + sizeof(ObsGrid) * (size_t)n);
     L.off_tables = off; off = up(off + sizeof(BPlan) * (size_t)n * (size_t)max_stages);
     L.off_bases = off; off = up(off + sizeof(uint64_t) * (size_t)n * (size_t)max_stages);
     L.off_jobs = off; off = up(off + sizeof(ExpandJob) * (size_t)n * (size_t)max_stages);
+    L.end_host = off;
+    L.off_grids = off; off = up(off + sizeof(ObsGrid) * (size_t)n);
     L.off_counters = off; off = up(off + sizeof(uint32_t) * kBatchStageCounters * (size_t)max_stages + 256);
     L.total = off;
     (void)o;
@@ -696,23 +700,21 @@ BatchLayout make_batch_layout(const gtmp_plan_desc *plans, int n, const gtmp_bat
 // An instantiated batch graph depends on everything the host put into its
 // kernel arguments and tables: the plan descriptors (sizes, policies, seeds,
 // device pointers), the options, the output buffers and the workspace.  A
-// call whose key matches an earlier one launches that graph again; the
-// tables it reads live in the workspace and are uploaded again only if
-// another batch wrote that workspace in between.  Graphs are kept for the
-// life of the process, at most kMaxBatchGraphs of them (later keys are
-// captured, launched, waited for and released as before).
+// call whose key matches an earlier one launches that graph again.  The
+// tables it reads live in the workspace, which belongs to the caller: they may
+// have freed it since, used it for something else and be passing the same
+// address again, so every launch is preceded by an asynchronous copy of the
+// tables, kept beside the graph in pinned memory (1 MB for 128 plans).  Graphs
+// are kept for the life of the process, at most kMaxBatchGraphs of them (later
+// keys are captured, launched, waited for and released).
 namespace {
 struct BatchGraph {
     hipGraphExec_t exec;
-    std::vector<ArmParams> arms;
-    std::vector<BPlan> host;
-    std::vector<uint64_t> bases;
-    std::vector<ExpandJob> jobs;
+    void *tables;  // pinned: workspace bytes [off_arm, end_host)
 };
 constexpr size_t kMaxBatchGraphs = 64;
 std::mutex g_batch_mu;
 std::map<std::string, BatchGraph> g_batch_graphs;
-std::map<const void *, std::string> g_batch_ws_owner;  // the key whose tables a workspace holds
 
 template <class T>
 void key_add(std::string &k, const T &v) {
@@ -736,21 +738,15 @@ std::string batch_key(const gtmp_plan_desc *plans, int n, const gtmp_batch_opts 
     return k;
 }
 
-hipError_t upload_tables(const BatchLayout &L, void *workspace, const std::vector<ArmParams> &arms,
-                         const std::vector<BPlan> &host, const std::vector<uint64_t> &bases,
-                         const std::vector<ExpandJob> &jobs, hipStream_t s) {
-    // after the work already on the stream (which may still read an earlier
-    // table) is done
-    char *ws = static_cast<char *>(workspace);
-    hipError_t err = hipStreamSynchronize(s);
-    if (err != hipSuccess) return err;
-    err = hipMemcpy(ws + L.off_arm, arms.data(), sizeof(ArmParams) * arms.size(), hipMemcpyHostToDevice);
-    if (err != hipSuccess) return err;
-    err = hipMemcpy(ws + L.off_tables, host.data(), sizeof(BPlan) * host.size(), hipMemcpyHostToDevice);
-    if (err != hipSuccess) return err;
-    err = hipMemcpy(ws + L.off_bases, bases.data(), sizeof(uint64_t) * bases.size(), hipMemcpyHostToDevice);
-    if (err != hipSuccess || jobs.empty()) return err;
-    return hipMemcpy(ws + L.off_jobs, jobs.data(), sizeof(ExpandJob) * jobs.size(), hipMemcpyHostToDevice);
+template <class T>
+void put_table(std::vector<char> &blob, size_t at, const std::vector<T> &v) {
+    if (!v.empty()) memcpy(blob.data() + at, v.data(), sizeof(T) * v.size());
+}
+
+hipError_t launch_kept(const BatchGraph &G, const BatchLayout &L, void *workspace, hipStream_t s) {
+    hipError_t e = hipMemcpyAsync(static_cast<char *>(workspace) + L.off_arm, G.tables, L.end_host - L.off_arm,
+                                  hipMemcpyHostToDevice, s);
+    return e == hipSuccess ? hipGraphLaunch(G.exec, s) : e;
 }
 }  // namespace
 
@@ -761,16 +757,7 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
         key = batch_key(plans, n, o, L, out, workspace);
         std::lock_guard<std::mutex> lk(g_batch_mu);
         auto it = g_batch_graphs.find(key);
-        if (it != g_batch_graphs.end()) {
-            auto ow = g_batch_ws_owner.find(workspace);
-            if (ow == g_batch_ws_owner.end() || ow->second != key) {
-                hipError_t err = upload_tables(L, workspace, it->second.arms, it->second.host, it->second.bases,
-                                               it->second.jobs, s);
-                if (err != hipSuccess) return err;
-                g_batch_ws_owner[workspace] = key;
-            }
-            return hipGraphLaunch(it->second.exec, s);
-        }
+        if (it != g_batch_graphs.end()) return launch_kept(it->second, L, workspace, s);
     }
     char *ws = static_cast<char *>(workspace);
     ArmParams *arm_dev = reinterpret_cast<ArmParams *>(ws + L.off_arm);
@@ -963,14 +950,17 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
     job_begin[L.max_stages] = jobs.size();
     const ExpandJob *jobs_dev = reinterpret_cast<const ExpandJob *>(ws + L.off_jobs);
 
-    // tables are written once, before any work is enqueued
-    hipError_t err = upload_tables(L, workspace, arms, host, host_bases, jobs, s);
+    // the tables, written before any work is enqueued and after the work
+    // already on the stream (which may still read an earlier table) is done
+    std::vector<char> blob(L.end_host - L.off_arm, 0);
+    put_table(blob, 0, arms);
+    put_table(blob, L.off_tables - L.off_arm, host);
+    put_table(blob, L.off_bases - L.off_arm, host_bases);
+    put_table(blob, L.off_jobs - L.off_arm, jobs);
+    hipError_t err = hipStreamSynchronize(s);
     if (err != hipSuccess) return err;
-    {
-        std::lock_guard<std::mutex> lk(g_batch_mu);
-        if (o.use_graph) g_batch_ws_owner[workspace] = key;
-        else g_batch_ws_owner.erase(workspace);
-    }
+    err = hipMemcpy(ws + L.off_arm, blob.data(), blob.size(), hipMemcpyHostToDevice);
+    if (err != hipSuccess) return err;
 
     // point robots: 8 states per lane and at most 3 resident blocks per CU
     // unless asked otherwise (as the single-plan launcher)
@@ -1101,10 +1091,12 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
     if (err != hipSuccess) return err;
     {
         std::lock_guard<std::mutex> lk(g_batch_mu);
-        if (g_batch_graphs.size() < kMaxBatchGraphs) {
-            g_batch_graphs.emplace(key, BatchGraph{exec, std::move(arms), std::move(host), std::move(host_bases),
-                                                   std::move(jobs)});
-            return hipGraphLaunch(exec, s);
+        void *pinned = nullptr;
+        if (g_batch_graphs.size() < kMaxBatchGraphs && hipHostMalloc(&pinned, blob.size(), 0) == hipSuccess) {
+            memcpy(pinned, blob.data(), blob.size());
+            const auto at = g_batch_graphs.emplace(key, BatchGraph{exec, pinned});
+            if (at.second) return hipGraphLaunch(exec, s);  // the tables are there already
+            (void)hipHostFree(pinned);  // another thread kept this key meanwhile
         }
     }
     err = hipGraphLaunch(exec, s);

@@ -208,7 +208,7 @@ struct BatchLayout {
     int n, max_stages;
     std::vector<PlanOffsets> plan_off;
     std::vector<std::vector<StageShape>> schedules;
-    size_t off_arm, off_grids, off_tables, off_bases, off_jobs, off_counters, total;
+    size_t off_arm, off_tables, off_bases, off_jobs, end_host, off_grids, off_counters, total;
 };
 BatchLayout make_batch_layout(const gtmp_plan_desc *plans, int n, const gtmp_batch_opts &o);
 struct BatchOut {
