@@ -8,7 +8,7 @@
 // they take (ball rejection, box rejection, pair order) are reproducible.
 #include <map>
 #include <mutex>
-#include <tuple>
+#include <string>
 
 #include "gtmp_launch.hpp"
 #include "rank.hpp"
@@ -799,14 +799,36 @@ AnytimePlan make_anytime_plan(const gtmp_problem &p, const gtmp_anytime_opts &o)
     return a;
 }
 
+// Captured restart stages, kept for the life of the process (at most
+// kMaxStageGraphs; a call past that captures, runs, waits and releases).  The
+// key is everything a stage's kernels are given: sizes, box, robot, scene,
+// options and every pointer.
 namespace {
-struct GraphKey {
-    std::tuple<const void *, const void *, const void *, const void *, uint64_t, int, int, int, int, int, hipStream_t>
-        k;
-    bool operator<(const GraphKey &o) const { return k < o.k; }
-};
+constexpr size_t kMaxStageGraphs = 64;
 std::mutex g_graph_mu;
-std::map<GraphKey, hipGraphExec_t> g_graphs;  // kept for the life of the process
+std::map<std::string, hipGraphExec_t> g_graphs;
+
+template <class T>
+void key_add(std::string &k, const T &v) {
+    k.append(reinterpret_cast<const char *>(&v), sizeof(T));
+}
+
+std::string stage_key(const gtmp_problem &p, const ArmParams *arm, const SceneParams &scene, int wdim, const float *q0,
+                      const float *goals, uint64_t seed, const gtmp_anytime_opts &o, const gtmp_edge_opts &eo,
+                      const AnytimeOut &out, const void *workspace, hipStream_t s) {
+    static_assert(sizeof(gtmp_problem) == (5 + 2 * GTMP_MAX_DOF + 2) * 4 && sizeof(ArmParams) % 4 == 0, "no padding");
+    std::string k;
+    key_add(k, p);
+    if (arm) key_add(k, *arm);
+    key_add(k, scene.sph); key_add(k, scene.box); key_add(k, scene.n_sph); key_add(k, scene.n_box);
+    key_add(k, wdim); key_add(k, q0); key_add(k, goals); key_add(k, seed);
+    key_add(k, o.max_stages); key_add(k, o.simplify);
+    key_add(k, eo.mode); key_add(k, eo.states_per_iter); key_add(k, eo.blocks_per_cu); key_add(k, eo.sphere_chunks);
+    key_add(k, eo.stats);
+    key_add(k, out.best_cost); key_add(k, out.best_idx); key_add(k, out.best_wp); key_add(k, out.best_meta);
+    key_add(k, out.stage_costs); key_add(k, workspace); key_add(k, s);
+    return k;
+}
 }  // namespace
 
 hipError_t launch_anytime(const gtmp_problem &p, const ArmParams *arm, const SceneParams &scene, int wdim,
@@ -883,12 +905,11 @@ hipError_t launch_anytime(const gtmp_problem &p, const ArmParams *arm, const Sce
             }
             return hipSuccess;
         }
-        // one stage captured on a private stream, instantiated once per
-        // (buffers, sizes, stream) and replayed max_stages times on `s`
-        GraphKey key{std::make_tuple((const void *)workspace, (const void *)q0, (const void *)goals,
-                                     (const void *)out.best_cost, seed, p.M, p.N, p.H, (int)eo.mode,
-                                     eo.sphere_chunks * 16 + eo.states_per_iter + (o.simplify ? 1 << 16 : 0), s)};
+        // one stage captured on a private stream, instantiated once and
+        // replayed max_stages times on `s`
+        const std::string key = stage_key(p, arm, scene, wdim, q0, goals, seed, o, eo, out, workspace, s);
         hipGraphExec_t exec = nullptr;
+        bool kept = true;
         {
             std::lock_guard<std::mutex> lk(g_graph_mu);
             auto it = g_graphs.find(key);
@@ -910,13 +931,16 @@ hipError_t launch_anytime(const gtmp_problem &p, const ArmParams *arm, const Sce
             (void)hipGraphDestroy(g);
             if (e != hipSuccess) return e;
             std::lock_guard<std::mutex> lk(g_graph_mu);
-            g_graphs[key] = exec;
+            kept = g_graphs.size() < kMaxStageGraphs && g_graphs.emplace(key, exec).second;
         }
-        for (int r = 0; r < o.max_stages; ++r) {
-            hipError_t e = hipGraphLaunch(exec, s);
-            if (e != hipSuccess) return e;
+        hipError_t e = hipSuccess;
+        for (int r = 0; r < o.max_stages && e == hipSuccess; ++r) e = hipGraphLaunch(exec, s);
+        if (!kept) {  // released once the stream has run it
+            const hipError_t w = hipStreamSynchronize(s);
+            if (e == hipSuccess) e = w;
+            (void)hipGraphExecDestroy(exec);
         }
-        return hipSuccess;
+        return e;
     }
 
     // growing budget (Alg. 1 ao-gtmp): the schedule is fixed, so the whole

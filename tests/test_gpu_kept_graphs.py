@@ -1,6 +1,7 @@
 """Kept graphs hold nothing of their callers' memory: a batch whose workspace
 was overwritten between two calls (as after being freed and allocated again at
-the same address)."""
+the same address) and a restart plan whose scene, robot or outputs changed
+while its workspace, samples' key and stream stayed."""
 import pytest
 import torch
 
@@ -25,3 +26,30 @@ def test_batch_workspace_overwritten_between_calls(gt):
         got = [x.clone() for x in (bp.best_cost, bp.best_idx, bp.best_wp, bp.best_meta, bp.stage_costs)]
         want = want or got
         assert all(torch.equal(a.nan_to_num(-7.0), b.nan_to_num(-7.0)) for a, b in zip(want, got)), fill
+
+
+@pytest.mark.parametrize("name", ["2d-small", "arm7"])
+def test_restart_graph_follows_scene_robot_and_outputs(gt, name):
+    print("[case] kept restart graph", name, flush=True)
+
+    def fresh(w):
+        ap = gt.AnytimePlanner(w, gt.GTMP_ANYTIME_RESTART, 3, use_graph=False)
+        ap.run(5)
+        return ap
+    w = wl.make_workload(name, 0, M=3, N=48)
+    other = wl.make_workload(name, 3, M=3, N=48)
+    ap = gt.AnytimePlanner(w, gt.GTMP_ANYTIME_RESTART, 3, use_graph=True)
+    ap.run(5)
+    assert torch.equal(ap.stage_costs, fresh(w).stage_costs)
+    # another scene (and robot), the start and goal written over in place
+    keep = ap.scene  # alive, so that a graph of the first call would read valid memory
+    ap.robot, ap.scene = gt.model_of(other)
+    ap.q0.copy_(torch.from_numpy(other["q0"]))
+    ap.goals.copy_(torch.from_numpy(other["goals"]))
+    ap.run(5)
+    assert torch.equal(ap.stage_costs, fresh(other).stage_costs)
+    # other outputs
+    old = ap.stage_costs
+    ap.stage_costs = torch.full_like(old, float("nan"))
+    ap.run(5)
+    assert torch.equal(ap.stage_costs, old) and keep is not None
