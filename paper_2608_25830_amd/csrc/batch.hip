@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t batch_cursor_begin(uint32_t n, uint32_t c) {
 struct BPlan {
     EdgeArgs A;          // edge check of this plan's stage (workspace, costs, tiles, t order)
     SceneParams S;
-    const ArmParams *arm;  // device copy of the robot table (arms), null for points
+    const ArmParams *arm;  // device copy of the robot table (arms: the ArmParams of an ArmTable), null for points
     float grid_r_max;      // arms: largest robot sphere radius (the obstacle bins are built for it); points: 0
     int group;           // 0: 2D point, 1: 3D point, 2: arm
     uint32_t vert_base;  // first vertex of this plan in its group's vertex space
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kWords > 1 ? 3 : (
     constexpr int WS = point_mask_stride<WG>();
     __shared__ typename std::conditional<GRID && ARM, GridMaskTable[4][WG], char>::type gmask;
     __shared__ typename std::conditional<GRID && !ARM, uint32_t[4][W][kGridCells][WS], char>::type pmask;
-    __shared__ typename std::conditional<GRID, GridQueue<WG>[4], char>::type gque;
+    __shared__ typename std::conditional<GRID, GridQueue<WG, ARM ? kQueueArm : kQueuePoint>[4], char>::type gque;
     const float4(*grec)[2] = nullptr;
     float ginv[3] = {0.f, 0.f, 0.f}, goff[3] = {0.f, 0.f, 0.f};
     uint32_t n_tests = 0;
@@ -368,7 +368,7 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kWords > 1 ? 3 : (
             const auto &R = *Rp;
             if constexpr (GRID) {
                 uint32_t tests = 0;
-                gap = arm_hit_grid<Model::kWords, UNIFORM_R>(R, q, gmask[wv], grec, ginv, goff, gque[wv], tests, has) ? -1.f : 1.f;
+                gap = arm_hit_grid<Model::kWords, UNIFORM_R>((ctable)Rp, q, gmask[wv], grec, gque[wv], tests, has) ? -1.f : 1.f;
                 n_tests += tests;
             } else {
                 const float r0 = R.r0;
@@ -574,25 +574,18 @@ __global__ void k_batch_init(const BPlan *plans, int n_plans) {
     *P.counter = 0;
 }
 
-// Rounding bound of the expanded sphere test per arm plan (see
-// k_store_params_tol): one wave per plan of the group range [p0, p1).
+// Rounding bound of the expanded sphere test and unreachable links per arm plan
+// (arm_scene_bounds): one wave per plan of the group range [p0, p1).
 __global__ void __launch_bounds__(64) k_batch_arm_tol(const BPlan *plans, int p0) {
     const BPlan &P = plans[p0 + blockIdx.x];
-    float cmax = 0.f, rmax = 0.f;
-    for (int o = threadIdx.x; o < P.S.n_sph; o += blockDim.x) {
-        const float *c = P.S.sph + 4 * o;
-        cmax = __builtin_fmaxf(cmax, __builtin_sqrtf(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]));
-        rmax = __builtin_fmaxf(rmax, __builtin_fabsf(c[3]));
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        cmax = __builtin_fmaxf(cmax, __shfl_xor(cmax, off));
-        rmax = __builtin_fmaxf(rmax, __shfl_xor(rmax, off));
-    }
-    if (threadIdx.x == 0) {
-        ArmParams *R = const_cast<ArmParams *>(P.arm);
-        const float pc = (R->reach + cmax) * 1.001f, rr = (rmax + R->r0) * 1.001f;
-        R->sph_tol = 0x1p-19f * (pc * pc + rr * rr);
+    ArmTable *T = reinterpret_cast<ArmTable *>(const_cast<ArmParams *>(P.arm));
+    float sph_tol;
+    int first_link;
+    arm_scene_bounds(T->R, P.S, sph_tol, first_link);
+    if (threadIdx.x == 0) T->R.sph_tol = sph_tol;
+    if ((int)threadIdx.x < first_link) {  // links no obstacle can reach: no spheres to look up
+        T->W.link[threadIdx.x].g.n = 0;
+        T->W.link[threadIdx.x].x_end = T->W.link[threadIdx.x].x_begin;
     }
 }
 
@@ -600,21 +593,15 @@ __global__ void __launch_bounds__(64) k_batch_arm_tol(const BPlan *plans, int p0
 // (one block per plan; the bins depend on the scene and the robot radii only).
 __global__ void __launch_bounds__(kGridBuildThreads) k_batch_build_grid(const BPlan *plans, int p0, int wdim) {
     const BPlan &P = plans[p0 + blockIdx.x];
-    build_grid_block(P.S, wdim, P.grid_r_max, const_cast<ObsGrid *>(P.A.grid));
+    const ArmTable *T = reinterpret_cast<const ArmTable *>(P.arm);
+    const GridBuild B = T ? grid_build_arm(P.grid_r_max, T->W.slack, T->R.reach, T->W.widen) : grid_build_points();
+    build_grid_block(P.S, wdim, B, const_cast<ObsGrid *>(P.A.grid));
+    if (T) store_arm_bins(P.A.grid, const_cast<ArmTable *>(T));
 }
 
 __global__ void k_batch_zero(uint32_t *p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
-}
-
-__global__ void k_store_params_n(const ArmParams *src, ArmParams *dst, int n) {
-    // src is a kernel-argument-free copy path: words of n structs
-    const uint32_t *s = reinterpret_cast<const uint32_t *>(src);
-    uint32_t *dd = reinterpret_cast<uint32_t *>(dst);
-    const size_t words = (size_t)n * (sizeof(ArmParams) / 4);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < words; i += (size_t)gridDim.x * blockDim.x)
-        dd[i] = s[i];
 }
 
 // ------------------------------------------------------------------ host side
@@ -684,7 +671,7 @@ BatchLayout make_batch_layout(const gtmp_plan_desc *plans, int n, const gtmp_bat
     }
     L.max_stages = max_stages;
     // the tables the host writes, together
-    L.off_arm = off; off = up(off + sizeof(ArmParams) * (size_t)n);
+    L.off_arm = off; off = up(off + sizeof(ArmTable) * (size_t)n);
     L.off_tables = off; off = up(off + sizeof(BPlan) * (size_t)n * (size_t)max_stages);
     L.off_bases = off; off = up(off + sizeof(uint64_t) * (size_t)n * (size_t)max_stages);
     L.off_jobs = off; off = up(off + sizeof(ExpandJob) * (size_t)n * (size_t)max_stages);
@@ -760,11 +747,10 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
         if (it != g_batch_graphs.end()) return launch_kept(it->second, L, workspace, s);
     }
     char *ws = static_cast<char *>(workspace);
-    ArmParams *arm_dev = reinterpret_cast<ArmParams *>(ws + L.off_arm);
+    ArmTable *arm_dev = reinterpret_cast<ArmTable *>(ws + L.off_arm);
     BPlan *tables = reinterpret_cast<BPlan *>(ws + L.off_tables);
     uint64_t *bases = reinterpret_cast<uint64_t *>(ws + L.off_bases);
     uint32_t *counters = reinterpret_cast<uint32_t *>(ws + L.off_counters);
-    (void)arm_dev;
 
     // ---- host tables of every stage (plans grouped: 2D points, 3D points, arms)
     std::vector<ArmParams> arms(arms_host, arms_host + n);
@@ -856,7 +842,7 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
                 A.n_int = interior_order(pp.H, ordr);
                 for (int i = 0; i < A.n_int; ++i) A.tord[i] = (float)ordr[i] / (float)(pp.H - 1);
                 B.S = SceneParams{D.scene.spheres, D.scene.boxes, D.scene.n_spheres, D.scene.n_boxes};
-                B.arm = gi == 2 ? arm_dev + p : nullptr;
+                B.arm = gi == 2 ? &arm_dev[p].R : nullptr;
                 if (gi == 0) {
                     A.grid = grids + p;  // point robot: bins for radius 0
                     B.grid_r_max = 0.f;
@@ -953,7 +939,10 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
     // the tables, written before any work is enqueued and after the work
     // already on the stream (which may still read an earlier table) is done
     std::vector<char> blob(L.end_host - L.off_arm, 0);
-    put_table(blob, 0, arms);
+    std::vector<ArmTable> tabs(n);
+    for (int p = 0; p < n; ++p)
+        if (group[p] == 2) tabs[p] = ArmTable{arms[p], make_arm_walk(arms[p])};
+    put_table(blob, 0, tabs);
     put_table(blob, L.off_tables - L.off_arm, host);
     put_table(blob, L.off_bases - L.off_arm, host_bases);
     put_table(blob, L.off_jobs - L.off_arm, jobs);

@@ -20,6 +20,8 @@
 //                     again (cost |v-u|, flag 0).
 // Full mode evaluates the exact signed distance of every state of every edge
 // (lanes = states, wave-level segmented min per edge) and writes minsd.
+#include <cmath>
+
 #include "edge_common.hpp"
 
 namespace gtmp {
@@ -52,7 +54,7 @@ __global__ void __launch_bounds__(256) k_wave_stats_sum(const unsigned long long
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     unsigned long long acc[3] = {0, 0, 0};
     if (i < waves)
-        for (int c = 0; c < 3; ++c) acc[c] = w[4 * (size_t)i + c];
+        for (int c = 0; c < 3; ++c) acc[c] = w[3 * (size_t)i + c];
     const int lane = lane_id(), wv = threadIdx.x / kWave;
     for (int c = 0; c < 3; ++c) {
 #pragma unroll
@@ -93,9 +95,9 @@ __device__ __forceinline__ void store_wave_stats(const EdgeArgs &A, unsigned lon
                                                  unsigned long long edges, unsigned long long tests) {
     const uint32_t wid = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (A.wstats && wid < kStatWaves) {
-        A.wstats[4 * (size_t)wid + 0] = states;
-        A.wstats[4 * (size_t)wid + 1] = edges;
-        A.wstats[4 * (size_t)wid + 2] = tests;
+        A.wstats[3 * (size_t)wid + 0] = states;
+        A.wstats[3 * (size_t)wid + 1] = edges;
+        A.wstats[3 * (size_t)wid + 2] = tests;
     } else {
         atomicAdd(&A.stats[0], states);
         atomicAdd(&A.stats[1], edges);
@@ -119,11 +121,62 @@ EdgePlan make_edge_plan(const gtmp_problem &p) {
     e.off_tile_off = o; o = up(o + (size_t)e.n_tiles * kTile);
     e.off_tile_cnt = o; o = up(o + sizeof(uint32_t) * (size_t)e.n_tiles);
     e.off_counter = o; o = up(o + sizeof(uint32_t) * kCursorStride * kCursors);
-    e.off_wstats = o; o = up(o + sizeof(unsigned long long) * 4 * kStatWaves);
-    e.off_params = o; o = up(o + sizeof(ArmParams));
+    e.off_wstats = o; o = up(o + sizeof(unsigned long long) * 3 * kStatWaves);
+    e.off_params = o; o = up(o + sizeof(ArmTable));
     e.off_grid = o; o = up(o + sizeof(ObsGrid));
     e.total = o;
     return e;
+}
+
+// Groups of the spheres for the obstacle bins: neighbours of a link are looked
+// up as one probe at their middle when their centres are at most 1.5 sphere
+// radii apart.  A pair's obstacles lie within the radius plus half that
+// distance, so on the arm of 40 spheres (0.045 m apart, radius 0.05) half the
+// lookups list 1.4 times the obstacles each (on centres spread over the scene);
+// farther apart the pairs' extra exact tests cost what the lookups save.
+ArmWalk make_arm_walk(const ArmParams &a) {
+    ArmWalk w{};
+    float r_max = 0.f;
+    for (int k = 0; k < a.n_spheres; ++k) r_max = std::max(r_max, a.r[k]);
+    double slack = 0.0, spread = 1.0;
+    uint32_t extra = 0;
+    for (int j = 0, k = 0; j < a.n_joints; ++j) {
+        ArmWalkLink &L = w.link[j];
+        L.off = a.off[j]; L.a = a.a[j]; L.dz = a.dz[j]; L.ca = a.ca[j]; L.sa = a.sa[j]; L.twist = a.twist[j];
+        L.x_begin = extra;
+        ArmGroups *G = &L.g;
+        G->k = (uint32_t)k;
+        const double len = std::sqrt((double)a.a[j] * a.a[j] + (double)a.dz[j] * a.dz[j]);
+        while (k < a.lk_end[j]) {
+            if (G->n == 4) {
+                G = &w.extra[extra++];
+                G->k = (uint32_t)k;
+            }
+            const uint32_t g = G->n++;
+            double t = a.t[k];
+            G->t[2 * g] = a.t[k];
+            if (k + 1 < a.lk_end[j]) {
+                const double half = 0.5 * std::fabs((double)a.t[k + 1] - t) * len;
+                if (half <= 0.75 * r_max) {
+                    t = 0.5 * (t + a.t[k + 1]);
+                    slack = std::max(slack, half);
+                    G->t[2 * g + 1] = a.t[++k];
+                    G->pairs |= 1u << g;
+                }
+            }
+            ++k;
+            G->tm[g] = (float)(t - 1.0);
+            spread = std::max(spread, std::fabs(t) + std::fabs(t - 1.0));
+        }
+        L.x_end = extra;
+    }
+    // rounded up, with room for the FP32 centres (1e-5 of the arm's reach)
+    w.slack = slack > 0.0 ? (float)(slack * (1.0 + 1e-6) + 1e-5 * a.reach) : 0.f;
+    // a probe's bin coordinate is a quarter bin per unit in the last place:
+    // its ends are off by at most one unit each, the sum by half of one
+    const double err = (spread + 0.5) / 4.0;
+    w.widen = err + 0.05 <= 1.0 ? 1 : (int)std::min(std::ceil(err + 0.05), 255.0);
+    return w;
 }
 
 int interior_order(int H, uint8_t *order) {
@@ -144,95 +197,55 @@ int interior_order(int H, uint8_t *order) {
     return n;
 }
 
-
-// Copy of the robot table (a kernel argument) into device memory.
-__global__ void k_store_params(ArmParams R, ArmParams *dst) {
+// The robot table for the interior kernel plus the tolerance of the expanded
+// sphere test and the links no obstacle can reach (arm_scene_bounds; one wave,
+// lanes 0..63 of the caller).  R and W are only read (the computed words are
+// substituted as the tables are copied), so they stay in kernel-argument
+// memory rather than being copied to per-lane scratch.
+__device__ __forceinline__ void store_params_tol_wave(const ArmParams &R, ArmParams *dst, const SceneParams &S,
+                                                      int &first_link) {
+    float sph_tol;
+    arm_scene_bounds(R, S, sph_tol, first_link);
     const uint32_t *src = reinterpret_cast<const uint32_t *>(&R);
     uint32_t *d = reinterpret_cast<uint32_t *>(dst);
     constexpr int n = sizeof(ArmParams) / 4;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) d[i] = src[i];
+    constexpr int w_tol = offsetof(ArmParams, sph_tol) / 4;
+    for (int i = threadIdx.x; i < n; i += kWave) d[i] = i == w_tol ? __float_as_uint(sph_tol) : src[i];
 }
 
-// The robot table for the interior kernel plus the tolerance of the expanded
-// sphere test: tol = 2^-19 ((reach + max|c|)^2 + (max r_o + r0)^2) over the
-// sphere obstacles (one wave, lanes 0..63 of the caller).  R is only read
-// (the two computed words are substituted as the table is copied), so it
-// stays in kernel-argument memory rather than being copied to per-lane
-// scratch.
-__device__ __forceinline__ void store_params_tol_wave(const ArmParams &R, ArmParams *dst, const SceneParams &S) {
-    const int lane = threadIdx.x;
-    float cmax = 0.f, rmax = 0.f;
-    for (int o = lane; o < S.n_sph; o += kWave) {
-        const float *c = S.sph + 4 * o;
-        cmax = __builtin_fmaxf(cmax, __builtin_sqrtf(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]));
-        rmax = __builtin_fmaxf(rmax, __builtin_fabsf(c[3]));
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        cmax = __builtin_fmaxf(cmax, __shfl_xor(cmax, off));
-        rmax = __builtin_fmaxf(rmax, __shfl_xor(rmax, off));
-    }
-    // rounding of the bound itself: inflate by 1e-3 relative
-    const float pc = (R.reach + cmax) * 1.001f, rr = (rmax + R.r0) * 1.001f;
-    const float sph_tol = 0x1p-19f * (pc * pc + rr * rr);
-    // Links near the base that no obstacle can reach: an obstacle (box of
-    // half-extents h around c, grown by rho) is at distance dist(0, box) - rho
-    // from the base, and a sphere of link L has |centre| <= link_reach[L-1];
-    // while every obstacle is farther than (link_reach + r_max) (1 + 1e-3) +
-    // 1e-6, no sphere of links 1..L can touch one (the exact test's rounding
-    // is far inside that margin), and the bin filter may skip them.
-    float dmin = __builtin_inff(), rk_max = 0.f;
-    for (int o = lane; o < S.n_sph + S.n_box; o += kWave) {
-        float dd;
-        if (o < S.n_sph) {
-            const float *c = S.sph + 4 * o;
-            dd = __builtin_sqrtf(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]) - __builtin_fabsf(c[3]);
-        } else {
-            const float *b = S.box + 6 * (o - S.n_sph);
-            float acc = 0.f;
-            for (int i = 0; i < 3; ++i) {
-                const float e = __builtin_fmaxf(__builtin_fabsf(b[i]) - __builtin_fabsf(b[3 + i]), 0.f);
-                acc += e * e;
-            }
-            dd = __builtin_sqrtf(acc);
-        }
-        dmin = __builtin_fminf(dmin, dd != dd ? -__builtin_inff() : dd);  // NaN data: nothing is skipped
-    }
-    for (int k = lane; k < R.n_spheres; k += kWave) rk_max = __builtin_fmaxf(rk_max, R.r[k]);
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        dmin = __builtin_fminf(dmin, __shfl_xor(dmin, off));
-        rk_max = __builtin_fmaxf(rk_max, __shfl_xor(rk_max, off));
-    }
-    int k_first = 0;
-    for (int L = 1; L <= R.n_joints; ++L) {
-        if (!(dmin > (R.link_reach[L - 1] + rk_max) * 1.001f + 1e-6f)) break;
-        k_first = R.lk_end[L - 1];
-    }
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(&R);
-    uint32_t *d = reinterpret_cast<uint32_t *>(dst);
-    constexpr int n = sizeof(ArmParams) / 4;
-    constexpr int w_tol = offsetof(ArmParams, sph_tol) / 4, w_first = offsetof(ArmParams, k_first) / 4;
-    for (int i = lane; i < n; i += kWave)
-        d[i] = i == w_tol ? __float_as_uint(sph_tol) : i == w_first ? (uint32_t)k_first : src[i];
+// Word i of the walk table, the links below first_link without spheres.
+__device__ __forceinline__ uint32_t walk_word(const uint32_t *src, int i, int first_link) {
+    constexpr int per = sizeof(ArmWalkLink) / 4;
+    const int L = i / per, w = i - L * per;
+    const bool count = w == (int)(offsetof(ArmWalkLink, g) + offsetof(ArmGroups, n)) / 4;
+    const bool end = w == (int)offsetof(ArmWalkLink, x_end) / 4;
+    if (L < first_link && L < GTMP_MAX_JOINTS && (count || end)) return count ? 0u : src[i - 1];  // x_end = x_begin
+    return src[i];
 }
 
 __global__ void __launch_bounds__(kWave) k_store_params_tol(ArmParams R, ArmParams *dst, SceneParams S) {
-    store_params_tol_wave(R, dst, S);
+    int first_link;
+    store_params_tol_wave(R, dst, S, first_link);
 }
 
-__global__ void __launch_bounds__(kGridBuildThreads) k_build_grid(SceneParams S, int wdim, float r_max,
-                                                                        ObsGrid *G) {
-    build_grid_block(S, wdim, r_max, G);
+__global__ void __launch_bounds__(kGridBuildThreads) k_build_grid(SceneParams S, int wdim, GridBuild B, ObsGrid *G) {
+    build_grid_block(S, wdim, B, G);
 }
 
 // An arm plan's obstacle bins (block 0) and its robot table with the sphere
 // test's tolerance (block 1, first wave) in one launch of two blocks:
 // neither reads what the other writes.
-__global__ void __launch_bounds__(kGridBuildThreads) k_build_grid_params(SceneParams S, float r_max, ObsGrid *G,
-                                                                         ArmParams R, ArmParams *dst) {
-    if (blockIdx.x == 0) build_grid_block(S, 3, r_max, G);
-    else if (threadIdx.x < kWave) store_params_tol_wave(R, dst, S);
+__global__ void __launch_bounds__(kGridBuildThreads) k_build_grid_params(SceneParams S, GridBuild B, ObsGrid *G,
+                                                                         ArmParams R, ArmWalk W, ArmTable *dst) {
+    if (blockIdx.x == 0) {
+        build_grid_block(S, 3, B, G);
+        store_arm_bins(G, dst);
+    } else if (threadIdx.x < kWave) {
+        int first_link;
+        store_params_tol_wave(R, &dst->R, S, first_link);
+        for (int i = threadIdx.x; i < (int)(offsetof(ArmWalk, bin) / 4); i += kWave)
+            reinterpret_cast<uint32_t *>(&dst->W)[i] = walk_word(reinterpret_cast<const uint32_t *>(&W), i, first_link);
+    }
 }
 
 // ------------------------------------------------------------------ 1. vertices
@@ -272,12 +285,12 @@ __global__ void __launch_bounds__(256) k_vertices_arm(EdgeArgs A, ArmParams R, S
 constexpr int kVertexGridWaves = 1;
 
 template <int WG>
-__global__ void __launch_bounds__(kVertexGridWaves * kWave) k_vertices_arm_grid(EdgeArgs A, ArmParams R,
+__global__ void __launch_bounds__(kVertexGridWaves * kWave) k_vertices_arm_grid(EdgeArgs A, const ArmTable *T,
                                                                                 const float *q0,
                                                                                 const float *goals, const float *Q,
                                                                                 float *verts, uint8_t *vflag) {
     __shared__ GridLds<WG> glds_raw;
-    __shared__ GridQueue<WG> gque[kVertexGridWaves];  // one queue per wave of the block
+    __shared__ ArmQueue<WG> gque[kVertexGridWaves];  // one queue per wave of the block
     // the vertex first, so that its loads and the bins' are in flight together
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < A.n_vertices;
@@ -298,14 +311,8 @@ __global__ void __launch_bounds__(kVertexGridWaves * kWave) k_vertices_arm_grid(
     }
     __syncthreads();
     const ObsGrid &G = *reinterpret_cast<const ObsGrid *>(&glds_raw);
-    float inv[3], off[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        inv[k] = G.inv[k];
-        off[k] = G.off[k];
-    }
     uint32_t tests = 0;
-    const bool hit = arm_hit_grid<WG>(R, q, G.mask, G.rec, inv, off, gque[wave_in_block()], tests, valid);
+    const bool hit = arm_hit_grid<WG>((ctable)T, q, G.mask, G.rec, gque[wave_in_block()], tests, valid);
     if (valid) vflag[i] = hit ? 1 : 0;
 }
 
@@ -370,7 +377,7 @@ __device__ __forceinline__ uint64_t list_states_limit() {
 constexpr int kListChunk = 4;
 
 template <class Model, bool UNIFORM_R, int NCH, bool LIST = false>
-__global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? 6 : 4) : NCH == 1 ? 3 : NCH == 2 ? 4 : 5)
+__global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWords == 1 ? 6 : 5) : 4) : NCH == 1 ? 3 : NCH == 2 ? 4 : 5)
     k_interior(EdgeArgs A, const ArmParams *Rg, SceneParams S) {
     constexpr int D = Model::D;
     constexpr int KP = Model::KP;
@@ -390,7 +397,7 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? 6 : 4) : NC
     // the mask words in pmask, one cell's words side by side
     __shared__ typename std::conditional<GRID, GridLds<ARM ? WG : 0>, char>::type glds_raw;
     __shared__ typename std::conditional<GRID && !ARM, PointMaskLds<WG>, char>::type pmask;
-    __shared__ typename std::conditional<GRID, GridQueue<WG>[256 / kWave], char>::type gque;
+    __shared__ typename std::conditional<GRID, GridQueue<WG, ARM ? kQueueArm : kQueuePoint>[256 / kWave], char>::type gque;
     const ObsGrid &glds = *reinterpret_cast<const ObsGrid *>(&glds_raw);  // the first grid_lds_bytes()
     for (int i = threadIdx.x; i < A.n_int; i += blockDim.x) tord[i] = A.tord[i];
     if constexpr (GRID) {  // the maps, the obstacles and the mask words this kernel reads
@@ -408,16 +415,7 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? 6 : 4) : NC
     }
     __syncthreads();
     float ginv[3] = {0.f, 0.f, 0.f}, goff[3] = {0.f, 0.f, 0.f};
-    if constexpr (GRID && Model::kArm) {
-        // wave-uniform and used once per link: the scales in scalar
-        // registers, the offsets in vector registers (an FMA reads one
-        // scalar operand)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            ginv[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(glds.inv[i])));
-            goff[i] = glds.off[i];
-        }
-    } else if constexpr (GRID) {
+    if constexpr (GRID && !ARM) {
         // point probes take both in one FMA per axis, which can read only one
         // scalar operand: vector registers avoid a copy per probe
 #pragma unroll
@@ -471,7 +469,7 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? 6 : 4) : NC
             if constexpr (GRID) {
                 uint32_t tests = 0;
                 const bool hit =
-                    arm_hit_grid<WG, UNIFORM_R && !LIST>(R, q, glds.mask, glds.rec, ginv, goff, gque[wv], tests, live);
+                    arm_hit_grid<WG, UNIFORM_R && !LIST>((ctable)Rp, q, glds.mask, glds.rec, gque[wv], tests, live);
                 n_tests += tests;
                 return hit ? -1.f : 1.f;
             } else {
@@ -779,7 +777,7 @@ __global__ void __launch_bounds__(kTile) k_finalize_no_interior(EdgeArgs A) {
 constexpr int kListBlocksPerCu = 6;
 
 template <class Model, bool UNIFORM_R, int NCH>
-__global__ void __launch_bounds__(256, Model::kArm && Model::kGrid ? 6 : 3) k_list_states(EdgeArgs A, const ArmParams *Rg, SceneParams S) {
+__global__ void __launch_bounds__(256, Model::kArm && Model::kGrid ? (Model::kWords == 1 ? 6 : 5) : 3) k_list_states(EdgeArgs A, const ArmParams *Rg, SceneParams S) {
     constexpr int D = Model::D;
     constexpr int KP = Model::KP;
     constexpr bool ARM = Model::kArm;
@@ -788,21 +786,13 @@ __global__ void __launch_bounds__(256, Model::kArm && Model::kGrid ? 6 : 3) k_li
     constexpr int WG = Model::kWords > 0 ? Model::kWords : 1;
     __shared__ float tord[GTMP_MAX_H];
     __shared__ typename std::conditional<GRID, GridLds<WG>, char>::type glds_raw;
-    __shared__ typename std::conditional<GRID, GridQueue<WG>[256 / kWave], char>::type gque;
+    __shared__ typename std::conditional<GRID, GridQueue<WG, ARM ? kQueueArm : kQueuePoint>[256 / kWave], char>::type gque;
     const ObsGrid &G = *reinterpret_cast<const ObsGrid *>(&glds_raw);
     for (int i = threadIdx.x; i < A.n_int; i += blockDim.x) tord[i] = A.tord[i];
     if constexpr (GRID) {
         copy_to_lds<grid_lds_bytes<WG>(), 256>(&glds_raw, A.grid, threadIdx.x);
     }
     __syncthreads();
-    float ginv[3] = {0.f, 0.f, 0.f}, goff[3] = {0.f, 0.f, 0.f};
-    if constexpr (GRID) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            ginv[i] = G.inv[i];
-            goff[i] = G.off[i];
-        }
-    }
     const int lane = lane_id();
     const uint32_t n_int = (uint32_t)A.n_int;
     const uint32_t waves = gridDim.x * (blockDim.x / kWave);
@@ -812,7 +802,7 @@ __global__ void __launch_bounds__(256, Model::kArm && Model::kGrid ? 6 : 3) k_li
         for (int i = threadIdx.x; i < kCursors * kCursorStride; i += 256) A.counter[i] = 0u;
         if (A.wstats)
             for (uint32_t i = waves + threadIdx.x; i < A.list_waves; i += 256)
-                for (int c = 0; c < 3; ++c) A.wstats[4 * (size_t)i + c] = 0ull;
+                for (int c = 0; c < 3; ++c) A.wstats[3 * (size_t)i + c] = 0ull;
     }
     const uint64_t all = (uint64_t)uniform(*A.n_list) * n_int;
     // long lists: the early-exit kernel takes them
@@ -839,7 +829,7 @@ __global__ void __launch_bounds__(256, Model::kArm && Model::kGrid ? 6 : 3) k_li
             asm volatile("" : "+s"(Rp));
             const auto &R = *Rp;
             if constexpr (GRID) {
-                hit = arm_hit_grid<Model::kWords, UNIFORM_R>(R, q, G.mask, G.rec, ginv, goff, gque[wave_in_block()],
+                hit = arm_hit_grid<Model::kWords, UNIFORM_R>((ctable)Rp, q, G.mask, G.rec, gque[wave_in_block()],
                                                              n_tests, live);
             } else {
                 const v32f o = arm_fk<D>(R, q);
@@ -1045,18 +1035,21 @@ static hipError_t launch_arm_kp(const EdgeArgs &A, const ArmParams &R, const Sce
     ObsGrid *grid = const_cast<ObsGrid *>(A.grid);
     if (phases & kPhaseVertices) {
         if (gw) {
+            const ArmWalk W = make_arm_walk(R);
             // the bins serve the vertex flags and, later, the interior kernel
             // (which also reads the robot table written beside them)
-            hipLaunchKernelGGL(k_build_grid_params, dim3(2), dim3(kGridBuildThreads), 0, s, S, r_max, grid, R, Rg);
+            hipLaunchKernelGGL(k_build_grid_params, dim3(2), dim3(kGridBuildThreads), 0, s, S,
+                               grid_build_arm(r_max, W.slack, R.reach, W.widen), grid, R, W,
+                               reinterpret_cast<ArmTable *>(Rg));
             // one wave per block: a plan has few vertices, so small blocks spread them over more CUs
             constexpr int vt = kVertexGridWaves * kWave;
             const unsigned vb64 = (A.n_vertices + vt - 1) / vt;
             if (gw == 1)
-                hipLaunchKernelGGL(k_vertices_arm_grid<1>, dim3(vb64), dim3(vt), 0, s, A, R, q0, goals, Q, verts,
-                                   vflag);
+                hipLaunchKernelGGL(k_vertices_arm_grid<1>, dim3(vb64), dim3(vt), 0, s, A,
+                                   reinterpret_cast<const ArmTable *>(Rg), q0, goals, Q, verts, vflag);
             else
-                hipLaunchKernelGGL(k_vertices_arm_grid<2>, dim3(vb64), dim3(vt), 0, s, A, R, q0, goals, Q, verts,
-                                   vflag);
+                hipLaunchKernelGGL(k_vertices_arm_grid<2>, dim3(vb64), dim3(vt), 0, s, A,
+                                   reinterpret_cast<const ArmTable *>(Rg), q0, goals, Q, verts, vflag);
         } else {
             hipLaunchKernelGGL(k_vertices_arm<KP>, dim3(vb), dim3(256), 0, s, A, R, S, q0, goals, Q, verts, vflag);
             hipLaunchKernelGGL(k_store_params_tol, dim3(1), dim3(kWave), 0, s, R, Rg, S);
@@ -1165,7 +1158,7 @@ static hipError_t launch_point(const EdgeArgs &A, const ArmParams &R, const Scen
     if (!(phases & kPhaseEdges)) return hipGetLastError();
     if (!A.edge_list) hipLaunchKernelGGL(k_prepass<W>, dim3(prepass_blocks(A)), dim3(kTile), 0, s, A);
     if (gw)  // the bins of the full check (lazy rounds keep the full test)
-        hipLaunchKernelGGL(k_build_grid, dim3(1), dim3(kGridBuildThreads), 0, s, S, W, 0.f,
+        hipLaunchKernelGGL(k_build_grid, dim3(1), dim3(kGridBuildThreads), 0, s, S, W, grid_build_points(),
                            const_cast<ObsGrid *>(A.grid));
     switch (spi) {
         case 1: return launch_point_s<W, 1>(A, R, S, grid_persist, o, s, gw);

@@ -170,7 +170,22 @@ __device__ __forceinline__ float arm_state_gap(const AP &R, const v32f &o, float
 // obstacle in every bin.
 constexpr int kGridBuildThreads = 3 * kGridCells;  // one (axis, bin) cell per thread
 
-__device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim, float r_max, ObsGrid *G) {
+// What the bins are built for: probes of radius r_max whose bins are looked up
+// at a point up to `slack` away (arms: a pair of spheres by its middle), the
+// obstacles' intervals widened by `widen` bins, and a probe region of radius
+// `reach` around the origin (0: unknown) over which bin coordinates stay below
+// 2^21, where the arms' lookups are exact to a quarter of a bin.
+struct GridBuild {
+    float r_max, slack, reach;
+    int widen;
+};
+__host__ __device__ inline GridBuild grid_build_points() { return GridBuild{0.f, 0.f, 0.f, 1}; }
+__host__ __device__ inline GridBuild grid_build_arm(float r_max, float slack, float reach, int widen) {
+    return GridBuild{r_max, slack, reach, widen};
+}
+
+__device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim, const GridBuild &B, ObsGrid *G) {
+    const float r_max = B.r_max;
     __shared__ float lo_s[kGridMaxObs][3], hi_s[kGridMaxObs][3];
     __shared__ int wild_s[kGridMaxObs];
     __shared__ int2 span_s[3][kGridMaxObs];  // bins listed for obstacle o on each axis
@@ -197,7 +212,7 @@ __device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim,
         // formed as the test forms it (R = rho + r, gap = -R R)
         const float Rr = rho + r_max;
         G->rec[tid][1] = make_float4(hi[0], hi[1], hi[2], -Rr * Rr);
-        const float ext = (__builtin_fabsf(rho) + r_max) * (1.f + 0x1p-12f);
+        const float ext = (__builtin_fabsf(rho) + r_max + B.slack) * (1.f + 0x1p-12f);
         bool wild = !__builtin_isfinite(ext);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
@@ -226,9 +241,11 @@ __device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim,
             b = 1.f;
         }
         // [a, b] -> f in [1, 254], the obstacles (four bins in) in about [5, 250]
+        // (an interval widened further than that stays within bins 1..254: a
+        // probe outside them is outside every obstacle's reach)
         constexpr float kSpan = (float)(kGridCells - 3);
         const float scale = __builtin_fmaxf(1.f, __builtin_fmaxf(__builtin_fabsf(a), __builtin_fabsf(b)));
-        const float span = __builtin_fmaxf(b - a, 1e-6f * scale);
+        const float span = __builtin_fmaxf(b - a, __builtin_fmaxf(1e-6f * scale, 0x1p-13f * B.reach));
         const float pad = span * (4.f / kSpan);
         a -= pad;
         b += pad;
@@ -242,8 +259,8 @@ __device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim,
         for (int o = l; o < n; o += kWave) {  // the obstacle's bins on this axis, one bin wider on each side
             int2 sp = make_int2(0, kGridCells - 1);  // non-finite obstacle or axis past the workspace: every bin
             if (!wild_s[o] && ax < wdim) {
-                sp.x = (int)grid_bin(__builtin_fmaf(lo_s[o][ax], inv, off)) - 1;
-                sp.y = (int)grid_bin(__builtin_fmaf(hi_s[o][ax], inv, off)) + 1;
+                sp.x = (int)grid_bin(__builtin_fmaf(lo_s[o][ax], inv, off)) - B.widen;
+                sp.y = (int)grid_bin(__builtin_fmaf(hi_s[o][ax], inv, off)) + B.widen;
                 sp.x = sp.x < 1 ? 1 : sp.x;
                 sp.y = sp.y > kGridCells - 2 ? kGridCells - 2 : sp.y;
             }
@@ -285,18 +302,23 @@ __device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim,
 // Every lane of the wave must call this (it drains on ballots), and Qw should
 // be addressed through a wave-uniform index, so that the queue's addresses
 // stay in scalar registers.
-constexpr int kQueue = 128;  // entries per wave: up to 63 waiting plus one probe of every lane
+// Entries per wave: up to 63 waiting plus one probe (arms: two) of every lane.
+constexpr int kQueuePoint = 128, kQueueArm = 192;
 
-template <int WORDS>
+template <int WORDS, int CAP>
 struct GridQueue {
     // one array per field: the centre with the first mask word beside it in
-    // one 16-byte entry (one store per probe; 2,372 bytes per wave with one
-    // mask word)
-    float4 c[kQueue];                                                // centre x, y, z; mask word 0 (bits)
-    uint32_t m[WORDS > 1 ? WORDS - 1 : 1][WORDS > 1 ? kQueue : 1];  // mask words 1 ..
-    uint16_t own[kQueue];                                            // owning lane | probe index << 8
+    // one 16-byte entry (one store per probe)
+    static constexpr int kWords = WORDS;
+    float4 c[CAP];                                                // centre x, y, z; mask word 0 (bits)
+    uint32_t m[WORDS > 1 ? WORDS - 1 : 1][WORDS > 1 ? CAP : 1];  // mask words 1 ..
+    uint16_t own[CAP];                                            // owning lane | probe index << 8
     uint8_t hit[kWave];
 };
+template <int WORDS>
+using ArmQueue = GridQueue<WORDS, kQueueArm>;
+template <int WORDS>
+using PointQueue = GridQueue<WORDS, kQueuePoint>;
 
 typedef uint32_t GridMaskTable[3][kGridCells];  // one mask word: axis, bin
 
@@ -307,9 +329,10 @@ typedef uint32_t GridMaskTable[3][kGridCells];  // one mask word: axis, bin
 // the queue needs no ring index.  rad(k) is the radius of probe k; UNI: every
 // probe has the radius the bins were built for (r_max), whose starting gap
 // the obstacle record holds, and entries carry no probe index.
-template <int WORDS, bool UNI, class Rad>
+template <class Queue, bool UNI, class Rad>
 struct GridProber {
-    GridQueue<WORDS> &Q;
+    static constexpr int WORDS = Queue::kWords;
+    Queue &Q;
     const float4 (*rec)[2];
     uint32_t &tests;
     const Rad &rad;
@@ -318,7 +341,7 @@ struct GridProber {
                           // not a bool, so that it stays a plain register across the loops
     uint64_t done;        // wave-uniform: the lanes that offer nothing more (hit, or not live)
 
-    __device__ __forceinline__ GridProber(GridQueue<WORDS> &q, const float4 (*r)[2], uint32_t &t, const Rad &rd,
+    __device__ __forceinline__ GridProber(Queue &q, const float4 (*r)[2], uint32_t &t, const Rad &rd,
                                           bool live)
         : Q(q), rec(r), tests(t), rad(rd), tail(0), hit(live ? 0u : 1u), done(ballot(!live)) {
         Q.hit[lane_id()] = 0;
@@ -385,34 +408,41 @@ struct GridProber {
         done = ballot(hit != 0);
     }
 
-    // This lane's probe k (bin mask words mw; centre(c) writes its centre,
-    // evaluated only for a queued probe): queued when some obstacle is listed
-    // and the lane's state is not known to collide.  The lanes to queue are
-    // found as one wave-wide mask (the compare's own lane mask less `done`),
-    // which is also the branch condition, so the common case of no lane
-    // queueing costs one vector compare.
-    template <class C>
-    __device__ __forceinline__ void offer(const uint32_t (&mw)[WORDS], uint32_t k, C &&centre) {
+    // This lane's probes (bin mask words mw): queued when some obstacle is
+    // listed and the lane's state is not known to collide.  push(r, n) stores
+    // a lane's entries at r and, when it has two, at n + r past the tail (r:
+    // its rank among the n lanes queueing); each lane has `per` of them.  The
+    // lanes to queue are found as one wave-wide mask (the compare's own lane
+    // mask less `done`), which is also the branch condition, so the common
+    // case of no lane queueing costs one vector compare.
+    template <class P>
+    __device__ __forceinline__ void offer(const uint32_t (&mw)[WORDS], uint32_t per, P &&push) {
         uint32_t any = mw[0];
 #pragma unroll
         for (int wd = 1; wd < WORDS; ++wd) any |= mw[wd];
         const uint64_t wmask = ballot(any != 0) & ~done;
         if (wmask != 0) {
-            if (__builtin_amdgcn_inverse_ballot_w64(wmask)) {  // any != 0 && hit == 0 in this lane
-                float c[3];
-                centre(c);
-                const int r = rank_in(wmask);
-                (&Q.c[tail])[r] = make_float4(c[0], c[1], c[2], __uint_as_float(mw[0]));
-#pragma unroll
-                for (int wd = 1; wd < WORDS; ++wd) (&Q.m[wd - 1][tail])[r] = mw[wd];
-                (&Q.own[tail])[r] = (uint16_t)(UNI ? (uint32_t)lane_id() : (uint32_t)lane_id() | k << 8);
-            }
-            tail += (uint32_t)__popcll(wmask);
-            if (tail >= (uint32_t)kWave) {
-                tail -= (uint32_t)kWave;
-                drain(tail, kWave);
-            }
+            const uint32_t n = (uint32_t)__popcll(wmask);
+            if (__builtin_amdgcn_inverse_ballot_w64(wmask)) push(rank_in(wmask), n);  // any != 0 && hit == 0 in this lane
+            tail += n * per;
         }
+    }
+
+    // Tests the waiting entries 64 at a time; after each offer (of up to two
+    // entries a lane).
+    __device__ __forceinline__ void drain_full() {
+        while (tail >= (uint32_t)kWave) {
+            tail -= (uint32_t)kWave;
+            drain(tail, kWave);
+        }
+    }
+
+    // One entry of this lane: probe k centred at c, `at` past the tail.
+    __device__ __forceinline__ void entry(int at, const uint32_t (&mw)[WORDS], const float (&c)[3], uint32_t k) {
+        (&Q.c[tail])[at] = make_float4(c[0], c[1], c[2], __uint_as_float(mw[0]));
+#pragma unroll
+        for (int wd = 1; wd < WORDS; ++wd) (&Q.m[wd - 1][tail])[at] = mw[wd];
+        (&Q.own[tail])[at] = (uint16_t)(UNI ? (uint32_t)lane_id() : (uint32_t)lane_id() | k << 8);
     }
 
     __device__ __forceinline__ bool finish() {
@@ -421,54 +451,136 @@ struct GridProber {
     }
 };
 
+// Bin maps of the arm lookups: with value = 2^23 + 4 f + 2 the low mantissa bits
+// of a probe's coordinate are 4 f + 2 rounded to an integer, so that
+// (bits & 0x3fc) is four times the bin nearest f, the byte offset of its mask
+// word: one AND where converting, clamping and scaling took two instructions.
+// A coordinate outside 0..255 wraps to some bin, whose obstacles the exact test
+// then refuses (out there a probe touches none); a NaN takes bin 0, which
+// lists none.
+__device__ __forceinline__ float arm_bin_scale(float inv) { return 4.f * inv; }
+__device__ __forceinline__ float arm_bin_offset(float off) { return __builtin_fmaf(4.f, off, 8388610.f); }
+// Writes the maps of the bins G to a robot table; for the block that built them.
+__device__ __forceinline__ void store_arm_bins(const ObsGrid *G, ArmTable *T) {
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        const int i = threadIdx.x & 3;
+        T->W.bin[threadIdx.x] = i == 3 ? 0.f : threadIdx.x < 4 ? arm_bin_scale(G->inv[i]) : arm_bin_offset(G->off[i]);
+    }
+}
+__device__ __forceinline__ uint32_t arm_mask_word(const uint32_t *cells, float value) {
+    return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(cells) + (__float_as_uint(value) & 0x3fcu));
+}
+
 // mk: the mask tables (mk[w] = word w), rec: the obstacle records; both may
-// live in LDS or in device memory.  The bin coordinate of a sphere centre
-// c = b + t (p - b) on axis i is taken as f = fp_i + (t - 1) (fp_i - fb_i),
-// fb and fp the bin coordinates of the link's ends (o_{L-1} and o_L, each
-// formed once: o_L's serves as the next link's fb); it differs from the
-// coordinate of the FP32 centre, c_i inv_i + off_i, by rounding only (below
-// 1e-4 of a bin for any centre within the bins' span), and every obstacle's
-// bin interval is widened by a bin on each side, so the bins still list
-// every obstacle the exact test can find in contact.  The centre itself,
-// fma(t, p - b, b) as the full test forms it, is formed only for the
-// spheres queued for an exact test.
-template <int WORDS, bool UNI = false, class AP>
-__device__ __forceinline__ bool arm_hit_grid(const AP &R, const float (&q)[GTMP_MAX_JOINTS],
-                                             const GridMaskTable *mk, const float4 (*rec)[2],
-                                             const float (&inv)[3], const float (&off)[3],
-                                             GridQueue<WORDS> &Qw, uint32_t &tests, bool live) {
+// live in LDS or in device memory.  Spheres are looked up by group (one or two
+// neighbours of a link, ArmWalk): the value of a group's middle b + t (p - b)
+// on axis i is taken as fp_i + (t - 1) (fp_i - fb_i), fb and fp the values of
+// the link's ends (o_{L-1} and o_L, each formed once: o_L's serves as the next
+// link's fb), each within one quarter of a bin; the obstacles' intervals are
+// widened to cover the middle's distance from its spheres and that error
+// (make_arm_walk), so the bins list every obstacle the exact test can find in
+// contact with a sphere of the group.  The centres themselves, fma(t, p - b, b)
+// as the full test forms them, are formed only for the groups queued for an
+// exact test.
+// Bound by vector issue (nine tenths of the cycles at six waves a SIMD).  M 8,
+// N 2048, 32.3 M states: a lookup per sphere, its parameters in 118 scalar
+// loads a state, took 1.20 ms; groups alone cut a sixth of the vector
+// instructions and no time (1.19 ms: the waves waited for those loads); two
+// vector loads a link and the next group's words requested before the current
+// group is worked on, 1.085 ms.  Requesting a link's parameters one link ahead
+// or seven waves a SIMD measured the same; a link's groups looked up all at
+// once spills (2.7 ms).
+// The link being walked: its joint, its groups and the bin maps.
+struct ArmWalker {
+    ctable T;
+    u32x8 head, bin;
+    u32x16 body;
+    typedef const __attribute__((address_space(4))) u32x8 *c8;
+    typedef const __attribute__((address_space(4))) u32x16 *c16;
+    __device__ __forceinline__ explicit ArmWalker(ctable t) : T(t) {}
+};
+__device__ __forceinline__ JointP joint_of(ArmWalker &A, int j) {
+    asm volatile("" : "+s"(A.T));  // the maps are read again for each link rather than held (and spilled)
+    A.head = *(ArmWalker::c8)&A.T->W.link[j];
+    A.body = *(ArmWalker::c16)&A.T->W.link[j].g;
+    A.bin = *(ArmWalker::c8)A.T->W.bin;
+    return JointP{__uint_as_float(A.head[0]), __uint_as_float(A.head[1]), __uint_as_float(A.head[2]),
+                  __uint_as_float(A.head[3]), __uint_as_float(A.head[4]), (int)A.head[5]};
+}
+
+template <int WORDS, bool UNI = false>
+__device__ __forceinline__ bool arm_hit_grid(ctable T, const float (&q)[GTMP_MAX_JOINTS],
+                                             const GridMaskTable *mk, const float4 (*rec)[2], ArmQueue<WORDS> &Qw,
+                                             uint32_t &tests, bool live) {
     // the radius of a queued sphere, read per lane when its tests are drained
-    const auto rad = [&](uint32_t k) { return R.r[k]; };
-    GridProber<WORDS, UNI, decltype(rad)> P(Qw, rec, tests, rad, live);
-    float fb[3] = {off[0], off[1], off[2]};  // o_0 = 0
-    arm_fk_visit<GTMP_MAX_JOINTS>(R, q, [&](int L, const float (&b)[3], const float (&p)[3]) {
+    const auto rad = [&](uint32_t k) { return T->R.r[k]; };
+    GridProber<ArmQueue<WORDS>, UNI, decltype(rad)> P(Qw, rec, tests, rad, live);
+    ArmWalker walk(T);
+    float fb[3] = {T->W.bin[4], T->W.bin[5], T->W.bin[6]};  // o_0 = 0
+    arm_fk_visit<GTMP_MAX_JOINTS>(walk, T->R.n_joints, q, [&](int, const float (&b)[3], const float (&p)[3]) {
         float fp[3], fd[3], d[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            fp[i] = __builtin_fmaf(p[i], inv[i], off[i]);
+            fp[i] = __builtin_fmaf(p[i], __uint_as_float(walk.bin[i]), __uint_as_float(walk.bin[4 + i]));
             fd[i] = fp[i] - fb[i];
             d[i] = p[i] - b[i];
             // formed once per link: kept in registers rather than re-formed
-            // in every iteration of the sphere loop below
+            // for every group below
             asm volatile("" : "+v"(fp[i]), "+v"(fd[i]), "+v"(d[i]));
         }
-        const int kl = L == 1 ? 0 : R.lk_end[L - 2];
-        const int k0 = kl > R.k_first ? kl : R.k_first;  // spheres below k_first reach no obstacle
-        const int k1 = R.lk_end[L - 1];
-        // unsigned index: the parameter address is a plain increment
-        for (uint32_t k = (uint32_t)k0; k < (uint32_t)k1; ++k) {
-            const float tm = R.tm1[k];
-            uint32_t bin[3];
+        auto groups = [&](const u32x16 &g) {
+            const uint32_t n = g[13], pairs = g[14];
+            if (n == 0) return;
+            auto look = [&](float tm, uint32_t (&raw)[WORDS][3]) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) bin[i] = grid_bin(__builtin_fmaf(tm, fd[i], fp[i]));
-            uint32_t mw[WORDS];
+                for (int i = 0; i < 3; ++i) {
+                    const float value = __builtin_fmaf(tm, fd[i], fp[i]);
 #pragma unroll
-            for (int wd = 0; wd < WORDS; ++wd) mw[wd] = mk[wd][0][bin[0]] & mk[wd][1][bin[1]] & mk[wd][2][bin[2]];
-            P.offer(mw, k, [&](float (&c)[3]) {
-                const float t = R.t[k];
+                    for (int wd = 0; wd < WORDS; ++wd) raw[wd][i] = arm_mask_word(mk[wd][i], value);
+                }
+            };
+            uint32_t mw[WORDS], first[WORDS][3];
+            look(__uint_as_float(g[0]), first);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(t, d[i], b[i]);
-            });
+            for (int wd = 0; wd < WORDS; ++wd) mw[wd] = first[wd][0] & first[wd][1] & first[wd][2];
+            uint32_t k = g[12], bits = pairs;
+            uint32_t tm1 = g[1], tm2 = g[2], tm3 = g[3];
+            uint32_t t0 = g[4], t1 = g[5], t2 = g[6], t3 = g[7], t4 = g[8], t5 = g[9], t6 = g[10], t7 = g[11];
+            // one copy of the probe and of the drain for the link's groups:
+            // the words of the next group are requested before the current
+            // ones are worked on, and its parameters shifted down
+#pragma nounroll
+            for (uint32_t left = n;;) {
+                uint32_t raw[WORDS][3];
+                if (left > 1) look(__uint_as_float(tm1), raw);
+                const uint32_t per = 1u + (bits & 1u);
+                P.offer(mw, per, [&](int r, uint32_t lanes) {
+                    float c[3];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(__uint_as_float(t0), d[i], b[i]);
+                    P.entry(r, mw, c, k);
+                    if (per == 2) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(__uint_as_float(t1), d[i], b[i]);
+                        P.entry(r + (int)lanes, mw, c, k + 1);
+                    }
+                });
+                P.drain_full();
+                if (--left == 0) break;
+#pragma unroll
+                for (int wd = 0; wd < WORDS; ++wd) mw[wd] = raw[wd][0] & raw[wd][1] & raw[wd][2];
+                k += per;
+                bits >>= 1;
+                tm1 = tm2; tm2 = tm3;
+                t0 = t2; t1 = t3; t2 = t4; t3 = t5; t4 = t6; t5 = t7;
+            }
+        };
+        groups(walk.body);
+        for (uint32_t x = walk.head[6]; x < walk.head[7]; ++x) {  // links of more than four groups
+            typedef const __attribute__((address_space(4))) u32x16 *c16;
+            const u32x16 g = *(c16)&T->W.extra[x];
+            groups(g);
         }
 #pragma unroll
         for (int i = 0; i < 3; ++i) fb[i] = fp[i];
@@ -485,10 +597,10 @@ __device__ __forceinline__ bool arm_hit_grid(const AP &R, const float (&q)[GTMP_
 template <int W, int SP, int WORDS, class AndMask>
 __device__ __forceinline__ bool point_hit_grid_by(const float (&p)[W][SP], const AndMask &and_mask,
                                                   const float4 (*rec)[2], const float (&inv)[3],
-                                                  const float (&off)[3], GridQueue<WORDS> &Qw, uint32_t &tests,
+                                                  const float (&off)[3], PointQueue<WORDS> &Qw, uint32_t &tests,
                                                   bool live) {
     const auto rad = [](uint32_t) { return 0.f; };
-    GridProber<WORDS, true, decltype(rad)> P(Qw, rec, tests, rad, live);
+    GridProber<PointQueue<WORDS>, true, decltype(rad)> P(Qw, rec, tests, rad, live);
 #pragma unroll
     for (int s = 0; s < SP; ++s) {
         float c[3] = {0.f, 0.f, 0.f};
@@ -503,10 +615,8 @@ __device__ __forceinline__ bool point_hit_grid_by(const float (&p)[W][SP], const
         for (int wd = 0; wd < WORDS; ++wd) mw[wd] = ~0u;
 #pragma unroll
         for (int i = 0; i < W; ++i) and_mask(i, bin[i], mw);
-        P.offer(mw, 0u, [&](float (&o)[3]) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) o[i] = c[i];
-        });
+        P.offer(mw, 1u, [&](int r, uint32_t) { P.entry(r, mw, c, 0u); });
+        P.drain_full();
     }
     return P.finish();
 }
@@ -517,7 +627,7 @@ template <int W, int SP, int WORDS, int AX>
 __device__ __forceinline__ bool point_hit_grid(const float (&p)[W][SP],
                                                const uint32_t (&pm)[AX][kGridCells][point_mask_stride<WORDS>()],
                                                const float4 (*rec)[2], const float (&inv)[3],
-                                               const float (&off)[3], GridQueue<WORDS> &Qw, uint32_t &tests,
+                                               const float (&off)[3], PointQueue<WORDS> &Qw, uint32_t &tests,
                                                bool live) {
     auto and_mask = [&](int i, uint32_t bin, uint32_t (&mw)[WORDS]) {
         const uint32_t *cell = pm[i][bin];
@@ -541,13 +651,61 @@ __device__ __forceinline__ bool point_hit_grid(const float (&p)[W][SP],
 template <int W, int SP, int WORDS>
 __device__ __forceinline__ bool point_hit_grid(const float (&p)[W][SP], const GridMaskTable *mk,
                                                const float4 (*rec)[2], const float (&inv)[3],
-                                               const float (&off)[3], GridQueue<WORDS> &Qw, uint32_t &tests,
+                                               const float (&off)[3], PointQueue<WORDS> &Qw, uint32_t &tests,
                                                bool live) {
     auto and_mask = [&](int i, uint32_t bin, uint32_t (&mw)[WORDS]) {
 #pragma unroll
         for (int wd = 0; wd < WORDS; ++wd) mw[wd] &= mk[wd][i][bin];
     };
     return point_hit_grid_by<W, SP, WORDS>(p, and_mask, rec, inv, off, Qw, tests, live);
+}
+
+// For one wave: the tolerance of the expanded sphere test,
+// tol = 2^-19 ((reach + max|c|)^2 + (max r_o + r0)^2) over the sphere obstacles,
+// and the links near the base that no obstacle can reach.  An obstacle (box of
+// half-extents h around c, grown by rho) is at distance dist(0, box) - rho
+// from the base, and a sphere of link L has |centre| <= link_reach[L-1]; while
+// every obstacle is farther than (link_reach + r_max) (1 + 1e-3) + 1e-6, no
+// sphere of links 1..L can touch one (the exact test's rounding is far inside
+// that margin), and the bin filter may skip them: first_link of them.
+__device__ __forceinline__ void arm_scene_bounds(const ArmParams &R, const SceneParams &S, float &sph_tol, int &first_link) {
+    const int lane = lane_id();
+    float cmax = 0.f, rmax = 0.f, dmin = __builtin_inff(), rk_max = 0.f;
+    for (int o = lane; o < S.n_sph + S.n_box; o += kWave) {
+        float dd;
+        if (o < S.n_sph) {
+            const float *c = S.sph + 4 * o;
+            const float r = __builtin_sqrtf(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]);
+            cmax = __builtin_fmaxf(cmax, r);
+            rmax = __builtin_fmaxf(rmax, __builtin_fabsf(c[3]));
+            dd = r - __builtin_fabsf(c[3]);
+        } else {
+            const float *b = S.box + 6 * (o - S.n_sph);
+            float acc = 0.f;
+            for (int i = 0; i < 3; ++i) {
+                const float e = __builtin_fmaxf(__builtin_fabsf(b[i]) - __builtin_fabsf(b[3 + i]), 0.f);
+                acc += e * e;
+            }
+            dd = __builtin_sqrtf(acc);
+        }
+        dmin = __builtin_fminf(dmin, dd != dd ? -__builtin_inff() : dd);  // NaN data: nothing is skipped
+    }
+    for (int k = lane; k < R.n_spheres; k += kWave) rk_max = __builtin_fmaxf(rk_max, R.r[k]);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        cmax = __builtin_fmaxf(cmax, __shfl_xor(cmax, off));
+        rmax = __builtin_fmaxf(rmax, __shfl_xor(rmax, off));
+        dmin = __builtin_fminf(dmin, __shfl_xor(dmin, off));
+        rk_max = __builtin_fmaxf(rk_max, __shfl_xor(rk_max, off));
+    }
+    // rounding of the bound itself: inflate by 1e-3 relative
+    const float pc = (R.reach + cmax) * 1.001f, rr = (rmax + R.r0) * 1.001f;
+    sph_tol = 0x1p-19f * (pc * pc + rr * rr);
+    first_link = 0;
+    for (int L = 1; L <= R.n_joints; ++L) {
+        if (!(dmin > (R.link_reach[L - 1] + rk_max) * 1.001f + 1e-6f)) break;
+        first_link = L;
+    }
 }
 
 // Row / tile decoding.  Rows enumerate the edges by their shared endpoint:

@@ -57,14 +57,49 @@ struct ArmParams {
     int twist[GTMP_MAX_JOINTS];                       // kind of twist (kTwist*): exact quarter turns take no arithmetic
     int link[GTMP_MAX_ROBOT_SPHERES];
     float t[GTMP_MAX_ROBOT_SPHERES];
-    float tm1[GTMP_MAX_ROBOT_SPHERES];  // t - 1: the sphere's place measured from the link's end
     float r[GTMP_MAX_ROBOT_SPHERES];
     int lk_end[GTMP_MAX_JOINTS];  // spheres of link L (1-based) are lk_end[L-2] .. lk_end[L-1]-1 (from 0 for L = 1)
     float reach;    // bound on |sphere centre|: sum of the link lengths sqrt(a^2 + d^2), rounded up
     float sph_tol;  // rounding bound of the expanded sphere test (set on the device per launch)
     float link_reach[GTMP_MAX_JOINTS];  // bound on |centre| of the spheres of link L (index L-1), rounded up
-    int k_first;    // spheres below this index can touch no obstacle of the scene (set on the device; 0 = unknown)
 };
+
+// What the bin-filtered arm test reads per link, packed so that a link takes two
+// scalar loads (make_arm_walk): the joint, and up to four groups of one or two
+// neighbouring spheres looked up together.  Groups past the fourth of a link
+// lie in extra[x_begin .. x_end).
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+struct ArmGroups {
+    float tm[4];      // fraction of the group's middle along the link, less 1
+    float t[8];       // of its spheres (t[2 g], t[2 g + 1])
+    uint32_t k;       // first sphere
+    uint32_t n;       // groups
+    uint32_t pairs;   // bit g: two spheres
+    uint32_t pad;
+};
+struct alignas(64) ArmWalkLink {
+    float off, a, dz, ca, sa;
+    int twist;
+    uint32_t x_begin, x_end;
+    uint32_t pad[8];
+    ArmGroups g;
+};
+struct alignas(64) ArmWalk {
+    ArmWalkLink link[GTMP_MAX_JOINTS];
+    ArmGroups extra[GTMP_MAX_ROBOT_SPHERES / 4];
+    float slack;   // bound on the distance of a sphere's centre from its group's, rounded up
+    int widen;     // bins an obstacle's interval is widened by on each side
+    uint32_t pad[6];
+    float bin[8];  // bin maps (scale on the three axes, 0, offset, 0), written by the kernel that builds the bins
+};
+static_assert(offsetof(ArmWalk, bin) % 32 == 0, "read as one 8-word vector");
+// The robot table in device memory.
+struct ArmTable {
+    ArmParams R;
+    ArmWalk W;
+};
+static_assert(sizeof(ArmGroups) == 64 && sizeof(ArmWalkLink) == 128, "read as one 8-word and one 16-word vector");
 
 // Obstacles: raw device arrays of the scene, spheres [n][wdim+1], boxes
 // [n][2*wdim].  They are read with wave-uniform indices through the constant
@@ -82,6 +117,7 @@ struct SceneParams {
 __device__ __forceinline__ cfp as_const(const float *p) { return (cfp)(p); }
 
 typedef const __attribute__((address_space(4))) struct ArmParams *carm;
+typedef const __attribute__((address_space(4))) struct ArmTable *ctable;
 
 // ---------------------------------------------------------------------------
 // Collision test of a set of KP probe spheres against every obstacle.
@@ -342,39 +378,49 @@ __device__ __forceinline__ void joint_sincos(float x, float &s, float &c) {
 // ---------------------------------------------------------------------------
 typedef float v32f __attribute__((ext_vector_type(32)));
 
+struct JointP {
+    float off, a, dz, ca, sa;
+    int twist;
+};
+template <class AP>
+__device__ __forceinline__ JointP joint_of(const AP &A, int j) {
+    return JointP{A.off[j], A.a[j], A.dz[j], A.ca[j], A.sa[j], A.twist[j]};
+}
+
 // Frame origins visited link by link: after joint j the visitor gets the link
 // index L = j + 1 and the origins o_{L-1} (b) and o_L (p) of that link.  The
 // first joint starts from the identity frame, written out (the general
 // update would multiply by the frame's zeros and ones, which floating point
 // cannot drop; the values are the same).
 template <int D, class AP, class F>
-__device__ __forceinline__ void arm_fk_visit(const AP &A, const float (&q)[D], F &&link) {
+__device__ __forceinline__ void arm_fk_visit(AP &A, int n_joints, const float (&q)[D], F &&link) {
     float x0 = 1.f, x1 = 0.f, x2 = 0.f;
     float y0 = 0.f, y1 = 1.f, y2 = 0.f;
     float z0 = 0.f, z1 = 0.f, z2 = 1.f;
     float p0 = 0.f, p1 = 0.f, p2 = 0.f;
 #pragma unroll
     for (int j = 0; j < D; ++j) {
-        if (j >= A.n_joints) break;
+        if (j >= n_joints) break;
+        const JointP J = joint_of(A, j);
         const float b[3] = {p0, p1, p2};
         float st, ct;
-        joint_sincos(q[j] + A.off[j], st, ct);
-        const float ca = A.ca[j], sa = A.sa[j];
+        joint_sincos(q[j] + J.off, st, ct);
+        const float ca = J.ca, sa = J.sa;
         if (j == 0) {
             x0 = ct; x1 = st; x2 = 0.f;
-            p0 = A.a[0] * ct; p1 = A.a[0] * st; p2 = A.dz[0];
+            p0 = J.a * ct; p1 = J.a * st; p2 = J.dz;
             y0 = -(ca * st); y1 = ca * ct; y2 = sa;
             z0 = sa * st; z1 = -(sa * ct); z2 = ca;
         } else {
             const float xn0 = ct * x0 + st * y0, xn1 = ct * x1 + st * y1, xn2 = ct * x2 + st * y2;
-            p0 += A.a[j] * xn0 + A.dz[j] * z0;
-            p1 += A.a[j] * xn1 + A.dz[j] * z1;
-            p2 += A.a[j] * xn2 + A.dz[j] * z2;
+            p0 += J.a * xn0 + J.dz * z0;
+            p1 += J.a * xn1 + J.dz * z1;
+            p2 += J.a * xn2 + J.dz * z2;
             {
                 const float yp0 = ct * y0 - st * x0, yp1 = ct * y1 - st * x1, yp2 = ct * y2 - st * x2;
                 // y' = ca yp + sa z, z' = ca z - sa yp; exact quarter turns and
                 // no twist give the same values without the products
-                const int tw = A.twist[j];
+                const int tw = J.twist;
                 if (tw == kTwistNone) {
                     y0 = yp0; y1 = yp1; y2 = yp2;
                 } else if (tw == kTwistPlus) {
@@ -403,7 +449,7 @@ __device__ __forceinline__ v32f arm_fk(const AP &A, const float (&q)[D]) {
     o[0] = 0.f;
     o[1] = 0.f;
     o[2] = 0.f;
-    arm_fk_visit<D>(A, q, [&](int L, const float (&)[3], const float (&p)[3]) {
+    arm_fk_visit<D>(A, A.n_joints, q, [&](int L, const float (&)[3], const float (&p)[3]) {
         o[3 * L + 0] = p[0];
         o[3 * L + 1] = p[1];
         o[3 * L + 2] = p[2];

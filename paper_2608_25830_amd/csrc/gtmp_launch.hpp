@@ -31,6 +31,9 @@ struct EdgePlan {
 
 EdgePlan make_edge_plan(const gtmp_problem &p);
 
+// The walk table of a robot (edge.hip).
+ArmWalk make_arm_walk(const ArmParams &R);
+
 struct EdgeBuffers {
     const float *q0, *goals, *Q;
     float *C_s, *C_h, *C_l;

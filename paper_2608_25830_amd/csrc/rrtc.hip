@@ -752,10 +752,10 @@ __global__ void __launch_bounds__(256) k_rrtc_vertices_bins(RrtcArgs A, const Ar
 }
 
 // The obstacle bins (block 0) and the robot table (block 1) in device memory.
-__global__ void __launch_bounds__(kGridBuildThreads) k_rrtc_bins(SceneParams S, float r_max, ObsGrid *G, ArmParams R,
+__global__ void __launch_bounds__(kGridBuildThreads) k_rrtc_bins(SceneParams S, GridBuild B, ObsGrid *G, ArmParams R,
                                                                  ArmParams *dst) {
     if (blockIdx.x == 0) {
-        build_grid_block(S, 3, r_max, G);
+        build_grid_block(S, 3, B, G);
         return;
     }
     const uint32_t *src = reinterpret_cast<const uint32_t *>(&R);
@@ -918,7 +918,8 @@ static hipError_t launch_rrtc_bins(const RrtcLaunch &L) {
     const uint32_t nv = rrtc_vertex_count(L.A), per = kRrtcStates * (256 / kWave);
     float r_max = 0.f;
     for (int k = 0; k < L.R.n_spheres; ++k) r_max = r_max > L.R.r[k] ? r_max : L.R.r[k];
-    hipLaunchKernelGGL(k_rrtc_bins, dim3(2), dim3(kGridBuildThreads), 0, L.s, L.S, r_max, L.grid, L.R, L.table);
+    hipLaunchKernelGGL(k_rrtc_bins, dim3(2), dim3(kGridBuildThreads), 0, L.s, L.S,
+                       grid_build_arm(r_max, 0.f, 0.f, 1), L.grid, L.R, L.table);
     hipLaunchKernelGGL(k_rrtc_vertices_bins<WORDS>, dim3((nv + per - 1) / per), dim3(256), 0, L.s, L.A, L.table, L.grid, nv,
                        L.vfree);
     launch_candidates(L);
