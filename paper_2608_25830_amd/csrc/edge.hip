@@ -440,7 +440,9 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWo
 
     // wave-uniform tile state
     uint32_t tile = 0, cnt = 0, pos = 0;
-    uint32_t cursor = blockIdx.x % kCursors, cursors_left = kCursors;
+    const bool wave_each = n_tiles <= gridDim.x * (blockDim.x / kWave);
+    uint32_t cursor = blockIdx.x % kCursors, cursors_left = wave_each ? 0u : (uint32_t)kCursors;
+    uint32_t first = wave_each ? blockIdx.x * (blockDim.x / kWave) + wv : n_tiles;  // the tile a wave has without asking
     RowInfo ri{};
     bool exhausted = false;
     // wave totals (wave-uniform, scalar registers): states evaluated, edges
@@ -535,20 +537,28 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWo
             if (avail == 0) {
                 // the tiles (lists: chunks) fall into kCursors ranges, each with
                 // its own cursor; a wave starts on its block's range and moves
-                // on to the next ones as they run dry
-                uint32_t t = 0;
-                bool got = false;
-                while (cursors_left > 0) {
-                    if (lane == 0) t = atomicAdd(A.counter + kCursorStride * cursor, 1u);
-                    t = uniform(t) + cursor_begin(n_tiles, cursor);
-                    if (t < cursor_begin(n_tiles, cursor + 1)) {
-                        got = true;
-                        break;
+                // on to the next ones as they run dry.  A grid with a wave for
+                // every tile hands them out by wave id: nine round trips to
+                // the cursors per wave, one tile and eight dry ranges, were
+                // half of a small plan's interior time (M 4, N 64: 17.0 us
+                // with them, 8.3 without; 3D, M 6, N 256: 42.6 and 32.6).  A
+                // larger grid keeps the turn: sending every wave straight to
+                // the ranges still open made them queue on the last one
+                // (2d-large, M 16, N 1024: 244 us in turn, 279).
+                uint32_t t = first;
+                first = n_tiles;
+                if (t >= n_tiles) {
+                    while (cursors_left > 0) {
+                        if (lane == 0) t = atomicAdd(A.counter + kCursorStride * cursor, 1u);
+                        t = uniform(t) + cursor_begin(n_tiles, cursor);
+                        if (t < cursor_begin(n_tiles, cursor + 1)) break;
+                        t = n_tiles;
+                        cursor = cursor + 1 < (uint32_t)kCursors ? cursor + 1 : 0u;
+                        --cursors_left;
                     }
-                    cursor = cursor + 1 < (uint32_t)kCursors ? cursor + 1 : 0u;
-                    --cursors_left;
                 }
-                if (!got) {
+                t = uniform(t);
+                if (t >= n_tiles) {
                     exhausted = true;
                     break;
                 }
@@ -744,7 +754,25 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWo
         for (int o = kWave / 2; o > 0; o >>= 1) counted += lane_read(lane ^ o, counted);
         n_states += uniform(counted);
     }
-    if (A.stats && lane == 0) store_wave_stats(A, n_states, n_edges, GRID ? n_tests : 0u);
+    if (!A.stats) return;
+    if (A.wstats || LIST) {
+        if (lane == 0) store_wave_stats(A, n_states, n_edges, GRID ? n_tests : 0u);
+        return;
+    }
+    // a small grid adds to the counters itself, once a block (a block's waves
+    // one by one queued on the counters' line for about 2 us)
+    __shared__ unsigned long long total[3][256 / kWave];
+    if (lane == 0) {
+        total[0][wv] = n_states;
+        total[1][wv] = n_edges;
+        total[2][wv] = GRID ? n_tests : 0u;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        unsigned long long t = 0;
+        for (int k = 0; k < 256 / kWave; ++k) t += total[threadIdx.x][k];
+        if (t) atomicAdd(&A.stats[threadIdx.x], t);
+    }
 }
 
 // Edges with H == 2 have no interior state: the pre-pass result is final

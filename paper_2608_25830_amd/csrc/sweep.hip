@@ -128,27 +128,33 @@ __global__ void __launch_bounds__(1024) k_start(int N, const float *__restrict__
 }
 
 // ---------------------------------------------------------------- small graphs
-// Whole recursion in one block of 256 threads; only for N <= 1024 (the
-// value buffers below hold one layer of at most 1024 entries each).  When C_h fits
-// (kSmallStage floats) the block first loads all of it into LDS in one
-// parallel burst, so the rows of a layer are not each a dependent global
-// load away.
+// Whole recursion in one block; only for N <= 1024 (the value buffers below
+// hold one layer of at most 1024 entries each, and a thread holds one start
+// edge) while C_h fits kSmallStage floats of LDS: the block first loads all of
+// it in one parallel burst, together with the goal and start edges, so that no
+// row is a dependent global load away.  What is left is latency: one trip to
+// memory, then M - 1 short passes over LDS.  Sixteen waves rather than four
+// take the burst in one trip and a fourth of the rows' columns each (M 4, N 64:
+// 10.4 us with four waves, 8.0 us with sixteen).
 constexpr int kSmallStage = 12288;
+constexpr int kSmallThreads = 1024;
 
-__global__ void __launch_bounds__(256) k_sweep_small(int M, int N, int G, const float *__restrict__ C_s,
-                                                     const float *__restrict__ C_h, const float *__restrict__ C_l,
-                                                     const float *__restrict__ Vg, float *V, int32_t *A, float *V_s,
-                                                     int32_t *a_s, int staged) {
+__global__ void __launch_bounds__(kSmallThreads) k_sweep_small(int M, int N, int G, const float *__restrict__ C_s,
+                                                               const float *__restrict__ C_h,
+                                                               const float *__restrict__ C_l,
+                                                               const float *__restrict__ Vg, float *V, int32_t *A,
+                                                               float *V_s, int32_t *a_s) {
     __shared__ __align__(16) float buf[2][1024];
-    __shared__ float sv[4];
-    __shared__ int si[4];
+    __shared__ float sv[kSmallThreads / kWave];
+    __shared__ int si[kSmallThreads / kWave];
     extern __shared__ float ch_lds[];
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
     float *cur = buf[0];
     float *nxt = buf[1];
-    if (staged) {
-        // eight independent 16-byte loads per thread in flight before their
+    const float cs = (int)threadIdx.x < N ? C_s[threadIdx.x] : 0.f;
+    {
+        // four independent 16-byte loads per thread in flight before their
         // LDS stores (a load-store loop would wait on every load in turn)
         const int n = (M - 1) * N * N;
         const int n4 = n >> 2;
@@ -156,23 +162,23 @@ __global__ void __launch_bounds__(256) k_sweep_small(int M, int N, int G, const 
         f4v *dst = reinterpret_cast<f4v *>(ch_lds);
         const bool vec = (reinterpret_cast<uintptr_t>(C_h) & 15) == 0;
         if (vec) {
-            for (int base = 0; base < n4; base += 8 * 256) {
-                f4v t[8];
+            constexpr int kLoads = (kSmallStage / 4 + kSmallThreads - 1) / kSmallThreads;
+            f4v t[kLoads];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int i = base + k * 256 + threadIdx.x;
-                    if (i < n4) t[k] = src[i];
-                }
+            for (int k = 0; k < kLoads; ++k) {
+                const int i = k * kSmallThreads + (int)threadIdx.x;
+                if (i < n4) t[k] = src[i];
+            }
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int i = base + k * 256 + threadIdx.x;
-                    if (i < n4) dst[i] = t[k];
-                }
+            for (int k = 0; k < kLoads; ++k) {
+                const int i = k * kSmallThreads + (int)threadIdx.x;
+                if (i < n4) dst[i] = t[k];
             }
         }
         for (int i = vec ? 4 * n4 + threadIdx.x : threadIdx.x; i < n; i += blockDim.x) ch_lds[i] = C_h[i];
     }
-    for (int u = threadIdx.x; u < N; u += blockDim.x) {
+    if ((int)threadIdx.x < N) {
+        const int u = threadIdx.x;
         Best b{__builtin_inff(), -1};
         for (int g = 0; g < G; ++g) take(b, C_l[(size_t)u * G + g] + (Vg ? Vg[g] : 0.f), g);
         V[(size_t)(M - 1) * N + u] = b.v;
@@ -180,53 +186,41 @@ __global__ void __launch_bounds__(256) k_sweep_small(int M, int N, int G, const 
         nxt[u] = b.v;
     }
     __syncthreads();
-    // staged: tpr threads per row (consecutive lanes, a power of two), each
-    // scanning its columns in increasing order, then a tpr-lane butterfly;
-    // otherwise one wave per row streaming from global memory
+    // tpr threads per row (consecutive lanes, a power of two), each scanning
+    // its columns in increasing order, then a tpr-lane butterfly
     int lg = 0;
-    while ((N << (lg + 1)) <= 256 && lg < 6) ++lg;
-    const int tpr = 1 << lg, sub = threadIdx.x & (tpr - 1), rows_per_pass = 256 >> lg;
+    while ((N << (lg + 1)) <= kSmallThreads && lg < 6) ++lg;
+    const int tpr = 1 << lg, sub = threadIdx.x & (tpr - 1), rows_per_pass = kSmallThreads >> lg;
     for (int m = M - 2; m >= 0; --m) {
-        if (staged) {
-            for (int u0 = 0; u0 < N; u0 += rows_per_pass) {
-                const int u = u0 + (threadIdx.x >> lg);
-                Best b{__builtin_inff(), -1};
-                if (u < N) {
-                    const float *row = ch_lds + ((size_t)m * N + u) * N;
-                    for (int v = sub; v < N; v += tpr) take(b, row[v] + nxt[v], v);
-                }
-                for (int off = tpr >> 1; off > 0; off >>= 1) {
-                    const float ov = __shfl_xor(b.v, off);
-                    const int oi = __shfl_xor(b.i, off);
-                    if (ov < b.v || (ov == b.v && (unsigned)oi < (unsigned)b.i)) { b.v = ov; b.i = oi; }
-                }
-                if (u < N && sub == 0) {
-                    V[(size_t)m * N + u] = b.v;
-                    A[(size_t)m * N + u] = b.i;
-                    cur[u] = b.v;
-                }
+        for (int u0 = 0; u0 < N; u0 += rows_per_pass) {
+            const int u = u0 + (threadIdx.x >> lg);
+            Best b{__builtin_inff(), -1};
+            if (u < N) {
+                const float *row = ch_lds + ((size_t)m * N + u) * N;
+                for (int v = sub; v < N; v += tpr) take(b, row[v] + nxt[v], v);
             }
-        } else {
-            for (int u = w; u < N; u += 4) {
-                const Best b = row_argmin(C_h + ((size_t)m * N + u) * N, nxt, N, lane);
-                if (lane == 0) {
-                    V[(size_t)m * N + u] = b.v;
-                    A[(size_t)m * N + u] = b.i;
-                    cur[u] = b.v;
-                }
+            for (int off = tpr >> 1; off > 0; off >>= 1) {
+                const float ov = __shfl_xor(b.v, off);
+                const int oi = __shfl_xor(b.i, off);
+                if (ov < b.v || (ov == b.v && (unsigned)oi < (unsigned)b.i)) { b.v = ov; b.i = oi; }
+            }
+            if (u < N && sub == 0) {
+                V[(size_t)m * N + u] = b.v;
+                A[(size_t)m * N + u] = b.i;
+                cur[u] = b.v;
             }
         }
         __syncthreads();
         float *t = cur; cur = nxt; nxt = t;
     }
     Best b{__builtin_inff(), -1};
-    for (int u = threadIdx.x; u < N; u += blockDim.x) take(b, C_s[u] + nxt[u], u);
+    if ((int)threadIdx.x < N) take(b, cs + nxt[threadIdx.x], threadIdx.x);
     b = wave_argmin(b);
     if (lane == 0) { sv[w] = b.v; si[w] = b.i; }
     __syncthreads();
     if (threadIdx.x == 0) {
         Best r{__builtin_inff(), -1};
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < kSmallThreads / kWave; ++k)
             if (sv[k] < r.v || (sv[k] == r.v && (unsigned)si[k] < (unsigned)r.i)) { r.v = sv[k]; r.i = si[k]; }
         *V_s = r.v;
         *a_s = r.i;
@@ -241,10 +235,9 @@ hipError_t launch_minplus(int M, int N, int G, const float *C_s, const float *C_
     // (N <= 1024: the block's two value buffers hold one layer each; at M = 1
     // the staging bound alone would admit any N)
     if (N <= 1024 && (long long)(M - 1) * N * N <= kSmallStage) {
-        const int staged = 1;
-        const size_t lds = staged ? sizeof(float) * (size_t)(M - 1) * N * N : 0;
-        hipLaunchKernelGGL(k_sweep_small, dim3(1), dim3(256), lds, s, M, N, G, C_s, C_h, C_l, Vg, V, A, V_s, a_s,
-                           staged);
+        const size_t lds = sizeof(float) * (size_t)(M - 1) * N * N;
+        hipLaunchKernelGGL(k_sweep_small, dim3(1), dim3(kSmallThreads), lds, s, M, N, G, C_s, C_h, C_l, Vg, V, A, V_s,
+                           a_s);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_goal_layer, dim3((N + 255) / 256), dim3(256), 0, s, M, N, G, C_l, Vg, V, A);
