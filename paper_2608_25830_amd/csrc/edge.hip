@@ -228,10 +228,6 @@ __global__ void __launch_bounds__(kWave) k_store_params_tol(ArmParams R, ArmPara
     store_params_tol_wave(R, dst, S, first_link);
 }
 
-__global__ void __launch_bounds__(kGridBuildThreads) k_build_grid(SceneParams S, int wdim, GridBuild B, ObsGrid *G) {
-    build_grid_block(S, wdim, B, G);
-}
-
 // An arm plan's obstacle bins (block 0) and its robot table with the sphere
 // test's tolerance (block 1, first wave) in one launch of two blocks:
 // neither reads what the other writes.
@@ -343,6 +339,21 @@ __global__ void __launch_bounds__(kTile) k_prepass(EdgeArgs A) {
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < kCursors * kCursorStride; i += kTile) A.counter[i] = 0u;
     prepass_block<D>(A, blockIdx.x);
+}
+
+// The pre-pass and, in one more block, the bins the interior kernel of a point
+// robot reads: neither reads what the other writes, and the pre-pass hides the
+// build (2d-large, M 16, N 1024: 29 and 12 us one after the other, 29 together;
+// 3D, M 6, N 256: 4.5 and 8.7, 13 together, a launch less).  The first block
+// builds, so that it starts with the others.
+template <int D>
+__global__ void __launch_bounds__(kTile) k_prepass_grid(EdgeArgs A, SceneParams S, GridBuild B, ObsGrid *G) {
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i < kCursors * kCursorStride; i += kTile) A.counter[i] = 0u;
+        build_grid_block(S, D, B, G);
+    } else {
+        prepass_block<D>(A, blockIdx.x - 1);
+    }
 }
 
 static inline unsigned prepass_blocks(const EdgeArgs &A) { return prepass_block_count(A); }
@@ -1184,10 +1195,11 @@ static hipError_t launch_point(const EdgeArgs &A, const ArmParams &R, const Scen
     if (phases & kPhaseVertices)
         hipLaunchKernelGGL(k_vertices_point<W>, dim3(vb), dim3(256), 0, s, A, S, q0, goals, Q, verts, vflag);
     if (!(phases & kPhaseEdges)) return hipGetLastError();
-    if (!A.edge_list) hipLaunchKernelGGL(k_prepass<W>, dim3(prepass_blocks(A)), dim3(kTile), 0, s, A);
-    if (gw)  // the bins of the full check (lazy rounds keep the full test)
-        hipLaunchKernelGGL(k_build_grid, dim3(1), dim3(kGridBuildThreads), 0, s, S, W, grid_build_points(),
+    if (gw && !A.edge_list)  // the bins of the full check (lazy rounds keep the full test)
+        hipLaunchKernelGGL(k_prepass_grid<W>, dim3(prepass_blocks(A) + 1), dim3(kTile), 0, s, A, S, grid_build_points(),
                            const_cast<ObsGrid *>(A.grid));
+    else if (!A.edge_list)
+        hipLaunchKernelGGL(k_prepass<W>, dim3(prepass_blocks(A)), dim3(kTile), 0, s, A);
     switch (spi) {
         case 1: return launch_point_s<W, 1>(A, R, S, grid_persist, o, s, gw);
         case 2: return launch_point_s<W, 2>(A, R, S, grid_persist, o, s, gw);

@@ -157,8 +157,8 @@ __device__ __forceinline__ float arm_state_gap(const AP &R, const v32f &o, float
 
 // The obstacle bins of a scene of dimension wdim (2 or 3) for robot spheres
 // of radius <= r_max (a point robot: 0), built by one block of
-// kGridBuildThreads threads (a thread per obstacle, then a wave per axis, then
-// a thread per (axis, bin) cell).  The bin maps and the obstacle intervals are
+// kGridBuildThreads threads or 256 (a thread per obstacle, then a wave per
+// axis, then the threads over the (axis, bin) cells).  The bin maps and the obstacle intervals are
 // computed in FP32 with the same fused multiply-add and bin rounding the
 // kernels apply to a probe centre (both monotone), and every interval is
 // widened by one bin on each side, so rounding in either place cannot move a
@@ -272,15 +272,35 @@ __device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim,
         G->off[3] = 0.f;
     }
     __syncthreads();
-    const int ax = tid / kGridCells, bin = tid - ax * kGridCells;
-    uint32_t w[3] = {0u, 0u, 0u};
     const bool all = bad_s != 0;
-    for (int o = 0; o < n; ++o) {
-        const int2 sp = span_s[ax][o];
-        if (all || (bin >= sp.x && bin <= sp.y)) w[o >> 5] |= 1u << (o & 31);
-    }
+    // a thread takes one cell, or (256 threads) its bin on the three axes in one
+    // pass over the obstacles, four of them at a time
+    auto fill = [&](auto cells) {
+        constexpr int P = decltype(cells)::value;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) G->mask[k][ax][bin] = w[k];
+        for (int k = 0; k < 3; ++k) {
+            uint32_t w[P];
+#pragma unroll
+            for (int c = 0; c < P; ++c) w[c] = 0u;
+            const int n_k = n - 32 * k < 32 ? n - 32 * k : 32;
+#pragma unroll 4
+            for (int o = 0; o < n_k; ++o) {
+#pragma unroll
+                for (int c = 0; c < P; ++c) {
+                    const int cell = tid + c * kGridCells, ax = cell / kGridCells, bin = cell - ax * kGridCells;
+                    const int2 sp = span_s[ax][32 * k + o];
+                    if (all || (bin >= sp.x && bin <= sp.y)) w[c] |= 1u << o;
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+                const int cell = tid + c * kGridCells, ax = cell / kGridCells, bin = cell - ax * kGridCells;
+                G->mask[k][ax][bin] = w[c];
+            }
+        }
+    };
+    if ((int)blockDim.x >= kGridBuildThreads) fill(std::integral_constant<int, 1>{});
+    else fill(std::integral_constant<int, 3>{});
 }
 
 // Collision of one arm state through the obstacle bins (G in LDS; inv / off
