@@ -71,11 +71,13 @@ def arm_grid_state_flops(n_joints, n_spheres, d):
     """Algorithmic FP32 operations of one arm state behind the obstacle bins,
     apart from the exact tests (FMA = 2, any other arithmetic op = 1):
       lerp                 2 d
-      DH FK per joint      48 + 1 + 2 as above, and the link vector 3 sub
-      per sphere           centre 3 fma + bin coordinates 3 fma + 3 clamps = 15
+      DH FK per joint      48 + 1 + 2 as above, the link vector 3 sub, its end's bin coordinates 3 fma and
+                           their difference 3 sub = 63
+      per sphere           3: bin coordinates 3 fma for a lookup, two neighbouring spheres to a lookup (spheres
+                           too far apart for that take one each, not counted; centres are formed for queued spheres only)
     Each exact sphere-obstacle test (counted by the kernel) adds
       GRID_TEST_FLOPS      R add + R^2 mul + 3 (med3 + sub + fma) + compare = 15"""
-    return 2 * d + 54 * n_joints + 15 * n_spheres
+    return 2 * d + 63 * n_joints + 3 * n_spheres
 
 
 GRID_TEST_FLOPS = 15
