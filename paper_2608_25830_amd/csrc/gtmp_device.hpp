@@ -387,6 +387,23 @@ __device__ __forceinline__ JointP joint_of(const AP &A, int j) {
     return JointP{A.off[j], A.a[j], A.dz[j], A.ca[j], A.sa[j], A.twist[j]};
 }
 
+// u v + x y and u v - x y of the kinematics, in the edge checks with the product
+// that is rounded written out (fk_first: the second, fk_last: the first).  Left
+// to the compiler it is another one wherever the code around it changes, and the
+// status of an edge that touches an obstacle to the last bit changes with it.
+// Files that define GTMP_FK_PLAIN keep the plain expressions: the local planner,
+// compiled without contraction, and path shortcutting, whose checks are compared
+// with no other kernel's.
+#ifdef GTMP_FK_PLAIN
+__device__ __forceinline__ float fk_first(float u, float v, float x, float y) { return u * v + x * y; }
+__device__ __forceinline__ float fk_last(float u, float v, float x, float y) { return u * v + x * y; }
+__device__ __forceinline__ float fk_diff(float u, float v, float x, float y) { return u * v - x * y; }
+#else
+__device__ __forceinline__ float fk_first(float u, float v, float x, float y) { return __builtin_fmaf(u, v, x * y); }
+__device__ __forceinline__ float fk_last(float u, float v, float x, float y) { return __builtin_fmaf(x, y, u * v); }
+__device__ __forceinline__ float fk_diff(float u, float v, float x, float y) { return __builtin_fmaf(u, v, -(x * y)); }
+#endif
+
 // Frame origins visited link by link: after joint j the visitor gets the link
 // index L = j + 1 and the origins o_{L-1} (b) and o_L (p) of that link.  The
 // first joint starts from the identity frame, written out (the general
@@ -412,12 +429,12 @@ __device__ __forceinline__ void arm_fk_visit(AP &A, int n_joints, const float (&
             y0 = -(ca * st); y1 = ca * ct; y2 = sa;
             z0 = sa * st; z1 = -(sa * ct); z2 = ca;
         } else {
-            const float xn0 = ct * x0 + st * y0, xn1 = ct * x1 + st * y1, xn2 = ct * x2 + st * y2;
-            p0 += J.a * xn0 + J.dz * z0;
-            p1 += J.a * xn1 + J.dz * z1;
-            p2 += J.a * xn2 + J.dz * z2;
+            const float xn0 = fk_last(ct, x0, st, y0), xn1 = fk_last(ct, x1, st, y1), xn2 = fk_last(ct, x2, st, y2);
+            p0 += fk_first(J.a, xn0, J.dz, z0);
+            p1 += fk_first(J.a, xn1, J.dz, z1);
+            p2 += fk_first(J.a, xn2, J.dz, z2);
             {
-                const float yp0 = ct * y0 - st * x0, yp1 = ct * y1 - st * x1, yp2 = ct * y2 - st * x2;
+                const float yp0 = fk_diff(ct, y0, st, x0), yp1 = fk_diff(ct, y1, st, x1), yp2 = fk_diff(ct, y2, st, x2);
                 // y' = ca yp + sa z, z' = ca z - sa yp; exact quarter turns and
                 // no twist give the same values without the products
                 const int tw = J.twist;
@@ -430,8 +447,8 @@ __device__ __forceinline__ void arm_fk_visit(AP &A, int n_joints, const float (&
                     y0 = -z0; y1 = -z1; y2 = -z2;
                     z0 = yp0; z1 = yp1; z2 = yp2;
                 } else {
-                    const float yn0 = ca * yp0 + sa * z0, yn1 = ca * yp1 + sa * z1, yn2 = ca * yp2 + sa * z2;
-                    const float zn0 = ca * z0 - sa * yp0, zn1 = ca * z1 - sa * yp1, zn2 = ca * z2 - sa * yp2;
+                    const float yn0 = fk_last(ca, yp0, sa, z0), yn1 = fk_last(ca, yp1, sa, z1), yn2 = fk_last(ca, yp2, sa, z2);
+                    const float zn0 = fk_diff(ca, z0, sa, yp0), zn1 = fk_diff(ca, z1, sa, yp1), zn2 = fk_diff(ca, z2, sa, yp2);
                     y0 = yn0; y1 = yn1; y2 = yn2;
                     z0 = zn0; z1 = zn1; z2 = zn2;
                 }

@@ -36,6 +36,7 @@
 // This file is compiled without floating-point contraction: sampling, nearest
 // node and steering are FP32 computations with a fixed operation order (see
 // include/gtmp.h), so the trees are reproducible bit for bit.
+#define GTMP_FK_PLAIN 1
 #include "edge_common.hpp"
 #include "state_test.hpp"
 

@@ -16,6 +16,7 @@
 //   k_shortcut_dp     one wave per path: lane j holds the cost-to-goal of
 //                     waypoint j, the backward recursion takes K - 1 wave
 //                     arg-min reductions, then the chain is followed from w_0.
+#define GTMP_FK_PLAIN 1
 #include "edge_common.hpp"
 #include "state_test.hpp"
 
