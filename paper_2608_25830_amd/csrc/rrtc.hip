@@ -301,7 +301,7 @@ __device__ __forceinline__ uint32_t arm_hit8(const AP &R, const SphereTab &T, co
                     const float dlt = c[i] - __builtin_amdgcn_fmed3f(c[i], ol[i], oh[i]);
                     g = __builtin_fmaf(dlt, dlt, g);
                 }
-                if (!(g > 0.f)) {
+                if (g <= 0.f) {  // a gap that is not a number is no contact, as in the general test's minimum
                     hit = true;
                     mm = 0;
                 }
@@ -757,6 +757,13 @@ __global__ void __launch_bounds__(kGridBuildThreads) k_rrtc_bins(SceneParams S, 
                                                                  ArmParams *dst) {
     if (blockIdx.x == 0) {
         build_grid_block(S, 3, B, G);
+        // a sphere whose centre is not a number touches nothing in the general
+        // test; as a box of that centre it would span the axis
+        const int o = threadIdx.x;  // the thread that wrote the record
+        if (o < S.n_sph) {
+            const float4 c = G->rec[o][0];
+            if (__builtin_isnan(c.x) || __builtin_isnan(c.y) || __builtin_isnan(c.z)) G->rec[o][0].w = __builtin_nanf("");
+        }
         return;
     }
     const uint32_t *src = reinterpret_cast<const uint32_t *>(&R);
