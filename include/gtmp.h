@@ -464,7 +464,11 @@ gtmp_status gtmp_anytime_workspace_size(const gtmp_problem *prob, const gtmp_any
  * [(M_max + 2) d] for the best stage's (M); best_meta [4] = (best stage, its
  * M, its N, stages run); stage_costs [max_stages].  prob->M, N give the
  * restart sizes; prob->G, H, d, box and penalty apply to both.  The whole
- * loop is enqueued on `stream` with no host synchronisation.
+ * loop is enqueued on `stream` with no host synchronisation.  With use_graph the
+ * captured stage is kept and replayed by later restart calls with the same
+ * problem, robot, options, stream and device pointers, whatever their seed; at
+ * most 64 are kept per process, and a call that finds no room enqueues its stages
+ * one by one.
  * With opts->simplify the archive holds shortcut paths (Alg. 1): restart
  * compares the stage path's cost with the archived cost and, when lower,
  * stores the shortcut of the stage path; growing shortcuts every stage path

@@ -685,19 +685,18 @@ hipError_t launch_informed_batch(const gtmp_problem &p, const float *q0, const f
 }
 
 // ------------------------------------------------------------------ one stage of a plan
-// Uniform layer samples with the stage number read from device memory
-// (stage = base + *counter), so that a captured stage can be replayed.
-__global__ void __launch_bounds__(256) k_sample_dev_stage(int M, int N, int d, uint32_t k0, uint32_t k1,
-                                                          const uint32_t *counter, uint32_t base, BoxArgs B,
+// Uniform layer samples with the stage number and the key read from device
+// memory (counter[0], then the key's two words), so that a captured stage can be
+// replayed for every stage and every seed.
+__global__ void __launch_bounds__(256) k_sample_dev_stage(int M, int N, int d, const uint32_t *counter, BoxArgs B,
                                                           float *__restrict__ Q) {
     const int nblk = (d + 3) >> 2;
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (tid >= (uint64_t)M * N * nblk) return;
-    const uint32_t stage = base + *counter;
     const uint32_t blk = (uint32_t)(tid % nblk);
     const uint64_t mn = tid / nblk;
     const uint32_t n = (uint32_t)(mn % N), m = (uint32_t)(mn / N);
-    const uint4 w = philox4x32_10(make_uint4(n, m, stage, blk), k0, k1);
+    const uint4 w = philox4x32_10(make_uint4(n, m, counter[0], blk), counter[1], counter[2]);
     float *dst = Q + mn * d;
     for (int i = 0; i < 4; ++i) {
         const int j = (int)blk * 4 + i;
@@ -734,14 +733,16 @@ __global__ void k_archive(int M, int N, int d, const float *cost, const int32_t 
     *counter = stage + 1;
 }
 
-__global__ void k_anytime_init(float *best_cost, int32_t *best_meta, uint32_t *counter) {
+__global__ void k_anytime_init(float *best_cost, int32_t *best_meta, uint32_t *counter, uint32_t k0, uint32_t k1) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     *best_cost = __builtin_inff();
     best_meta[0] = -1;
     best_meta[1] = 0;
     best_meta[2] = 0;
     best_meta[3] = 0;
-    *counter = 0;
+    counter[0] = 0;
+    counter[1] = k0;
+    counter[2] = k1;
 }
 
 // ------------------------------------------------------------------ drivers
@@ -799,14 +800,28 @@ AnytimePlan make_anytime_plan(const gtmp_problem &p, const gtmp_anytime_opts &o)
     return a;
 }
 
-// Captured restart stages, kept for the life of the process (at most
-// kMaxStageGraphs; a call past that captures, runs, waits and releases).  The
-// key is everything a stage's kernels are given: sizes, box, robot, scene,
-// options and every pointer.
+// Captured restart stages.  The key is everything a stage's kernels are given:
+// sizes, box, robot, scene, options and every pointer; the seed is read from
+// device memory.  At most kMaxStageGraphs are kept.  No call waits for the device:
+// past that a call with another key enqueues its stages one by one (the same
+// kernels), unless some graph has been left unused for kStageGraphIdle calls and
+// its last launch has ended, which is then released for the new one.  (Releasing
+// the least recently used at once would have a program that goes round more
+// plans than are kept capture a stage on every call, which takes longer than
+// enqueuing it.)
 namespace {
 constexpr size_t kMaxStageGraphs = 64;
+constexpr uint64_t kStageGraphIdle = 256;
+
+struct StageGraph {
+    hipGraphExec_t exec;
+    hipEvent_t done;   // behind the latest launch
+    uint64_t last;     // the call that used it last
+    int users;         // calls between acquire and release
+};
 std::mutex g_graph_mu;
-std::map<std::string, hipGraphExec_t> g_graphs;
+std::map<std::string, StageGraph> g_graphs;
+uint64_t g_graph_calls = 0;
 
 template <class T>
 void key_add(std::string &k, const T &v) {
@@ -814,20 +829,75 @@ void key_add(std::string &k, const T &v) {
 }
 
 std::string stage_key(const gtmp_problem &p, const ArmParams *arm, const SceneParams &scene, int wdim, const float *q0,
-                      const float *goals, uint64_t seed, const gtmp_anytime_opts &o, const gtmp_edge_opts &eo,
-                      const AnytimeOut &out, const void *workspace, hipStream_t s) {
+                      const float *goals, const gtmp_anytime_opts &o, const gtmp_edge_opts &eo, const AnytimeOut &out,
+                      const void *workspace, hipStream_t s) {
     static_assert(sizeof(gtmp_problem) == (5 + 2 * GTMP_MAX_DOF + 2) * 4 && sizeof(ArmParams) % 4 == 0, "no padding");
     std::string k;
     key_add(k, p);
     if (arm) key_add(k, *arm);
     key_add(k, scene.sph); key_add(k, scene.box); key_add(k, scene.n_sph); key_add(k, scene.n_box);
-    key_add(k, wdim); key_add(k, q0); key_add(k, goals); key_add(k, seed);
+    key_add(k, wdim); key_add(k, q0); key_add(k, goals);
     key_add(k, o.max_stages); key_add(k, o.simplify);
     key_add(k, eo.mode); key_add(k, eo.states_per_iter); key_add(k, eo.blocks_per_cu); key_add(k, eo.sphere_chunks);
     key_add(k, eo.stats);
     key_add(k, out.best_cost); key_add(k, out.best_idx); key_add(k, out.best_wp); key_add(k, out.best_meta);
     key_add(k, out.stage_costs); key_add(k, workspace); key_add(k, s);
     return k;
+}
+
+// The kept graph of a key, held until stage_graph_release, or NULL; room: a
+// graph captured now can be kept.
+StageGraph *stage_graph_acquire(const std::string &key, bool *room) {
+    std::lock_guard<std::mutex> lk(g_graph_mu);
+    const uint64_t now = ++g_graph_calls;
+    auto it = g_graphs.find(key);
+    *room = true;
+    if (it != g_graphs.end()) {
+        it->second.last = now;
+        ++it->second.users;
+        return &it->second;
+    }
+    if (g_graphs.size() < kMaxStageGraphs) return nullptr;
+    auto old = g_graphs.end();
+    for (auto e = g_graphs.begin(); e != g_graphs.end(); ++e)
+        if (e->second.users == 0 && (old == g_graphs.end() || e->second.last < old->second.last)) old = e;
+    *room = false;
+    if (old != g_graphs.end() && now - old->second.last > kStageGraphIdle) {
+        // (relaxed: the question concerns no capture that another thread may be making)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        *room = hipEventQuery(old->second.done) == hipSuccess;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (*room) {
+        (void)hipGraphExecDestroy(old->second.exec);
+        (void)hipEventDestroy(old->second.done);
+        g_graphs.erase(old);
+    }
+    return nullptr;
+}
+
+// Keeps a captured graph under its key and holds it, or releases it (NULL):
+// another thread kept this key or took the room meanwhile.
+StageGraph *stage_graph_keep(const std::string &key, hipGraphExec_t exec) {
+    hipEvent_t done = nullptr;
+    if (hipEventCreateWithFlags(&done, hipEventDisableTiming) == hipSuccess) {
+        std::lock_guard<std::mutex> lk(g_graph_mu);
+        if (g_graphs.size() < kMaxStageGraphs) {
+            const auto at = g_graphs.emplace(key, StageGraph{exec, done, g_graph_calls, 1});
+            if (at.second) return &at.first->second;
+        }
+    }
+    if (done) (void)hipEventDestroy(done);
+    (void)hipGraphExecDestroy(exec);
+    return nullptr;
+}
+
+void stage_graph_release(StageGraph *g, hipStream_t s) {
+    // a graph whose end cannot be told is never given up
+    const bool told = hipEventRecord(g->done, s) == hipSuccess;
+    std::lock_guard<std::mutex> lk(g_graph_mu);
+    if (told) --g->users;
 }
 }  // namespace
 
@@ -856,9 +926,9 @@ hipError_t launch_anytime(const gtmp_problem &p, const ArmParams *arm, const Sce
     eo.ev_begin = nullptr;
     eo.ev_end = nullptr;
     const int d = p.d;
-    const uint32_t k0 = (uint32_t)(seed & 0xffffffffu), k1 = (uint32_t)(seed >> 32);
 
-    hipLaunchKernelGGL(k_anytime_init, dim3(1), dim3(64), 0, s, out.best_cost, out.best_meta, counter);
+    hipLaunchKernelGGL(k_anytime_init, dim3(1), dim3(64), 0, s, out.best_cost, out.best_meta, counter,
+                       (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
 
     auto one_plan = [&](const gtmp_problem &pp, const float *Qp, hipStream_t st) -> hipError_t {
         const EdgePlan ep = make_edge_plan(pp);
@@ -894,28 +964,23 @@ hipError_t launch_anytime(const gtmp_problem &p, const ArmParams *arm, const Sce
         const uint64_t total = (uint64_t)p.M * p.N * ((d + 3) / 4);
         const unsigned sblocks = (unsigned)((total + 255) / 256);
         auto stage_ops = [&](hipStream_t st) -> hipError_t {
-            hipLaunchKernelGGL(k_sample_dev_stage, dim3(sblocks), dim3(256), 0, st, p.M, p.N, d, k0, k1, counter, 0u, B,
-                               Q);
+            hipLaunchKernelGGL(k_sample_dev_stage, dim3(sblocks), dim3(256), 0, st, p.M, p.N, d, counter, B, Q);
             return one_plan(p, Q, st);
         };
-        if (!o.use_graph || o.lp) {
+        auto all_stages = [&]() -> hipError_t {
             for (int r = 0; r < o.max_stages; ++r) {
                 hipError_t e = stage_ops(s);
                 if (e != hipSuccess) return e;
             }
             return hipSuccess;
-        }
+        };
+        if (!o.use_graph || o.lp) return all_stages();
         // one stage captured on a private stream, instantiated once and
         // replayed max_stages times on `s`
-        const std::string key = stage_key(p, arm, scene, wdim, q0, goals, seed, o, eo, out, workspace, s);
-        hipGraphExec_t exec = nullptr;
-        bool kept = true;
-        {
-            std::lock_guard<std::mutex> lk(g_graph_mu);
-            auto it = g_graphs.find(key);
-            if (it != g_graphs.end()) exec = it->second;
-        }
-        if (!exec) {
+        const std::string key = stage_key(p, arm, scene, wdim, q0, goals, o, eo, out, workspace, s);
+        bool room = false;
+        StageGraph *kept = stage_graph_acquire(key, &room);
+        if (!kept && room) {
             hipStream_t cs;
             hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
             if (e != hipSuccess) return e;
@@ -927,19 +992,16 @@ hipError_t launch_anytime(const gtmp_problem &p, const ArmParams *arm, const Sce
             (void)hipStreamDestroy(cs);
             if (e_ops != hipSuccess) { if (g) (void)hipGraphDestroy(g); return e_ops; }
             if (e != hipSuccess) return e;
+            hipGraphExec_t exec = nullptr;
             e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess) return e;
-            std::lock_guard<std::mutex> lk(g_graph_mu);
-            kept = g_graphs.size() < kMaxStageGraphs && g_graphs.emplace(key, exec).second;
+            kept = stage_graph_keep(key, exec);
         }
+        if (!kept) return all_stages();
         hipError_t e = hipSuccess;
-        for (int r = 0; r < o.max_stages && e == hipSuccess; ++r) e = hipGraphLaunch(exec, s);
-        if (!kept) {  // released once the stream has run it
-            const hipError_t w = hipStreamSynchronize(s);
-            if (e == hipSuccess) e = w;
-            (void)hipGraphExecDestroy(exec);
-        }
+        for (int r = 0; r < o.max_stages && e == hipSuccess; ++r) e = hipGraphLaunch(kept->exec, s);
+        stage_graph_release(kept, s);
         return e;
     }
 
