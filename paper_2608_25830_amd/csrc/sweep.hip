@@ -133,20 +133,24 @@ __global__ void __launch_bounds__(1024) k_start(int N, const float *__restrict__
 // edge) while C_h fits kSmallStage floats of LDS: the block first loads all of
 // it in one parallel burst, together with the goal and start edges, so that no
 // row is a dependent global load away.  What is left is latency: one trip to
-// memory, then M - 1 short passes over LDS.  Sixteen waves rather than four
-// take the burst in one trip and a fourth of the rows' columns each (M 4, N 64:
-// 10.4 us with four waves, 8.0 us with sixteen).
+// memory, then M - 1 short passes over LDS.  From layers of 33 vertices on,
+// sixteen waves rather than four take the burst in one trip and a fourth of the
+// rows' columns each (M 4, N 64: 10.4 us with four waves, 8.0 us with sixteen; M
+// 8, N 40: 12.1 and 11.0).  Smaller layers are a pass of one or two columns a
+// thread for four waves already; twelve more only wait at its barrier (M 12, N 16:
+// 11.2 us with four waves, 17.0 with sixteen; M 13, N 32: 13.7 and 16.8).
 constexpr int kSmallStage = 12288;
-constexpr int kSmallThreads = 1024;
+constexpr int kSmallFewThreads = 256, kSmallThreads = 1024;
+constexpr int kSmallFewMaxN = 32;
 
-__global__ void __launch_bounds__(kSmallThreads) k_sweep_small(int M, int N, int G, const float *__restrict__ C_s,
-                                                               const float *__restrict__ C_h,
-                                                               const float *__restrict__ C_l,
-                                                               const float *__restrict__ Vg, float *V, int32_t *A,
-                                                               float *V_s, int32_t *a_s) {
+template <int kThreads>
+__global__ void __launch_bounds__(kThreads) k_sweep_small(int M, int N, int G, const float *__restrict__ C_s,
+                                                          const float *__restrict__ C_h, const float *__restrict__ C_l,
+                                                          const float *__restrict__ Vg, float *V, int32_t *A,
+                                                          float *V_s, int32_t *a_s) {
     __shared__ __align__(16) float buf[2][1024];
-    __shared__ float sv[kSmallThreads / kWave];
-    __shared__ int si[kSmallThreads / kWave];
+    __shared__ float sv[kThreads / kWave];
+    __shared__ int si[kThreads / kWave];
     extern __shared__ float ch_lds[];
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
@@ -162,16 +166,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_sweep_small(int M, int N, int
         f4v *dst = reinterpret_cast<f4v *>(ch_lds);
         const bool vec = (reinterpret_cast<uintptr_t>(C_h) & 15) == 0;
         if (vec) {
-            constexpr int kLoads = (kSmallStage / 4 + kSmallThreads - 1) / kSmallThreads;
+            constexpr int kLoads = (kSmallStage / 4 + kThreads - 1) / kThreads;
             f4v t[kLoads];
 #pragma unroll
             for (int k = 0; k < kLoads; ++k) {
-                const int i = k * kSmallThreads + (int)threadIdx.x;
+                const int i = k * kThreads + (int)threadIdx.x;
                 if (i < n4) t[k] = src[i];
             }
 #pragma unroll
             for (int k = 0; k < kLoads; ++k) {
-                const int i = k * kSmallThreads + (int)threadIdx.x;
+                const int i = k * kThreads + (int)threadIdx.x;
                 if (i < n4) dst[i] = t[k];
             }
         }
@@ -189,8 +193,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_sweep_small(int M, int N, int
     // tpr threads per row (consecutive lanes, a power of two), each scanning
     // its columns in increasing order, then a tpr-lane butterfly
     int lg = 0;
-    while ((N << (lg + 1)) <= kSmallThreads && lg < 6) ++lg;
-    const int tpr = 1 << lg, sub = threadIdx.x & (tpr - 1), rows_per_pass = kSmallThreads >> lg;
+    while ((N << (lg + 1)) <= kThreads && lg < 6) ++lg;
+    const int tpr = 1 << lg, sub = threadIdx.x & (tpr - 1), rows_per_pass = kThreads >> lg;
     for (int m = M - 2; m >= 0; --m) {
         for (int u0 = 0; u0 < N; u0 += rows_per_pass) {
             const int u = u0 + (threadIdx.x >> lg);
@@ -220,7 +224,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_sweep_small(int M, int N, int
     __syncthreads();
     if (threadIdx.x == 0) {
         Best r{__builtin_inff(), -1};
-        for (int k = 0; k < kSmallThreads / kWave; ++k)
+        for (int k = 0; k < kThreads / kWave; ++k)
             if (sv[k] < r.v || (sv[k] == r.v && (unsigned)si[k] < (unsigned)r.i)) { r.v = sv[k]; r.i = si[k]; }
         *V_s = r.v;
         *a_s = r.i;
@@ -236,8 +240,12 @@ hipError_t launch_minplus(int M, int N, int G, const float *C_s, const float *C_
     // the staging bound alone would admit any N)
     if (N <= 1024 && (long long)(M - 1) * N * N <= kSmallStage) {
         const size_t lds = sizeof(float) * (size_t)(M - 1) * N * N;
-        hipLaunchKernelGGL(k_sweep_small, dim3(1), dim3(kSmallThreads), lds, s, M, N, G, C_s, C_h, C_l, Vg, V, A, V_s,
-                           a_s);
+        if (N <= kSmallFewMaxN)
+            hipLaunchKernelGGL(k_sweep_small<kSmallFewThreads>, dim3(1), dim3(kSmallFewThreads), lds, s, M, N, G, C_s, C_h,
+                               C_l, Vg, V, A, V_s, a_s);
+        else
+            hipLaunchKernelGGL(k_sweep_small<kSmallThreads>, dim3(1), dim3(kSmallThreads), lds, s, M, N, G, C_s, C_h, C_l,
+                               Vg, V, A, V_s, a_s);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_goal_layer, dim3((N + 255) / 256), dim3(256), 0, s, M, N, G, C_l, Vg, V, A);
