@@ -943,9 +943,11 @@ static hipError_t launch_rrtc_kernels(const RrtcLaunch &L, bool single) {
     const int obs = L.S.n_sph * (PW + 1) + L.S.n_box * 2 * PW;
     const uint32_t tab = obs <= kRrtcLdsObstacles ? (uint32_t)sizeof(float) * obs : 0u;
     const RrtcLayout Y = rrtc_layout(L.A.d, 2 * L.A.cap, 1, 0u, tab, false);
-    // 8 blocks (two waves per SIMD) fit in the 160 KiB of LDS of a CU?
-    const bool two = Y.total * 8 <= 163840;
-    const auto kern = two ? k_rrtc<ARM, W, KP, 0, 1, 2> : k_rrtc<ARM, W, KP, 0, 1, 1>;
+    // registers for one wave a SIMD: an arm's spheres take all 256 (made for
+    // two waves it spills 66 of them; 97 obstacles, M 3, N 48, trees of 256,
+    // budget 60: 2.47 ms against 3.25 for 40 spheres, 4.38 against 5.67 for 64,
+    // the same up to 24), a point's 96 leave room for five either way
+    const auto kern = k_rrtc<ARM, W, KP, 0, 1, 1>;
     if (single) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Y.total);
         if (e != hipSuccess) return e;
