@@ -226,7 +226,8 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kWords > 1 ? 3 : (
     constexpr int WS = point_mask_stride<WG>();
     __shared__ typename std::conditional<GRID && ARM, GridMaskTable[4][WG], char>::type gmask;
     __shared__ typename std::conditional<GRID && !ARM, uint32_t[4][W][kGridCells][WS], char>::type pmask;
-    __shared__ typename std::conditional<GRID, GridQueue<WG, ARM ? kQueueArm : kQueuePoint>[4], char>::type gque;
+    constexpr bool GROUPS = arm_by_groups<Model>();
+    __shared__ typename std::conditional<GRID, GridQueue<WG, GROUPS ? kQueueArm : kQueuePoint>[4], char>::type gque;
     const float4(*grec)[2] = nullptr;
     float ginv[3] = {0.f, 0.f, 0.f}, goff[3] = {0.f, 0.f, 0.f};
     uint32_t n_tests = 0;
@@ -368,7 +369,12 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kWords > 1 ? 3 : (
             const auto &R = *Rp;
             if constexpr (GRID) {
                 uint32_t tests = 0;
-                gap = arm_hit_grid<Model::kWords, UNIFORM_R>((ctable)Rp, q, gmask[wv], grec, gque[wv], tests, has) ? -1.f : 1.f;
+                bool hit;
+                if constexpr (GROUPS)
+                    hit = arm_hit_grid<WG, UNIFORM_R>((ctable)Rp, q, gmask[wv], grec, gque[wv], tests, has);
+                else
+                    hit = arm_hit_spheres<WG, UNIFORM_R>((ctable)Rp, q, gmask[wv], grec, ginv, goff, gque[wv], tests, has);
+                gap = hit ? -1.f : 1.f;
                 n_tests += tests;
             } else {
                 const float r0 = R.r0;
@@ -587,6 +593,7 @@ __global__ void __launch_bounds__(64) k_batch_arm_tol(const BPlan *plans, int p0
         T->W.link[threadIdx.x].g.n = 0;
         T->W.link[threadIdx.x].x_end = T->W.link[threadIdx.x].x_begin;
     }
+    if (threadIdx.x == 0) T->W.k_first = first_link > 0 ? T->R.lk_end[first_link - 1] : 0;
 }
 
 // Obstacle bins of every arm plan of the group range [p0, p0 + gridDim.x)
@@ -940,8 +947,12 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
     // already on the stream (which may still read an earlier table) is done
     std::vector<char> blob(L.end_host - L.off_arm, 0);
     std::vector<ArmTable> tabs(n);
+    bool by_groups = false;  // some robot's lookups are worth grouping: the kernel for groups serves the others too
     for (int p = 0; p < n; ++p)
-        if (group[p] == 2) tabs[p] = ArmTable{arms[p], make_arm_walk(arms[p])};
+        if (group[p] == 2) {
+            tabs[p] = ArmTable{arms[p], make_arm_walk(arms[p])};
+            by_groups = by_groups || tabs[p].W.by_groups != 0;
+        }
     put_table(blob, 0, tabs);
     put_table(blob, L.off_tables - L.off_arm, host);
     put_table(blob, L.off_bases - L.off_arm, host_bases);
@@ -1036,12 +1047,10 @@ hipError_t launch_batch(const gtmp_plan_desc *plans, const ArmParams *arms_host,
                 GTMP_BK(8) GTMP_BK(16) GTMP_BK(24) GTMP_BK(32) GTMP_BK(40) GTMP_BK(48) GTMP_BK(56) GTMP_BK(64)
 #undef GTMP_BK
 #undef GTMP_BK1
-                if (grid_words == 1)
-                    k = uniform_r ? (const void *)k_batch_interior<ArmGridModel<1>, true, 1>
-                                  : (const void *)k_batch_interior<ArmGridModel<1>, false, 1>;
-                if (grid_words == 2)
-                    k = uniform_r ? (const void *)k_batch_interior<ArmGridModel<2>, true, 1>
-                                  : (const void *)k_batch_interior<ArmGridModel<2>, false, 1>;
+#define GTMP_BG(MODEL) (uniform_r ? (const void *)k_batch_interior<MODEL, true, 1> : (const void *)k_batch_interior<MODEL, false, 1>)
+                if (grid_words == 1) k = by_groups ? GTMP_BG(ArmGridModel<1>) : GTMP_BG(ArmSphereModel<1>);
+                if (grid_words == 2) k = by_groups ? GTMP_BG(ArmGridModel<2>) : GTMP_BG(ArmSphereModel<2>);
+#undef GTMP_BG
                 if (!k) return hipErrorInvalidValue;
                 const int grid = persistent_blocks(k, o.blocks_per_cu);
                 uint32_t *c2 = ctr + 2 * kBatchGroupCounters;

@@ -129,17 +129,22 @@ EdgePlan make_edge_plan(const gtmp_problem &p) {
 }
 
 // Groups of the spheres for the obstacle bins: neighbours of a link are looked
-// up as one probe at their middle when their centres are at most 1.5 sphere
+// up as one probe at their middle when their centres are at most 2.5 sphere
 // radii apart.  A pair's obstacles lie within the radius plus half that
 // distance, so on the arm of 40 spheres (0.045 m apart, radius 0.05) half the
-// lookups list 1.4 times the obstacles each (on centres spread over the scene);
-// farther apart the pairs' extra exact tests cost what the lookups save.
-ArmWalk make_arm_walk(const ArmParams &a) {
+// lookups list 1.4 times the obstacles each (on centres spread over the scene).
+// M 8, N 1024, 24 spheres 0.08 m apart: 367 us with pairs, 431 without; 12 spheres
+// 0.16 m apart: 381 with pairs, 365 without.
+static ArmWalk group_spheres(const ArmParams &a, double reach_radii, int &lookups) {
     ArmWalk w{};
     float r_max = 0.f;
-    for (int k = 0; k < a.n_spheres; ++k) r_max = std::max(r_max, a.r[k]);
+    for (int k = 0; k < a.n_spheres; ++k) {
+        r_max = std::max(r_max, a.r[k]);
+        w.tm1[k] = a.t[k] - 1.f;
+    }
     double slack = 0.0, spread = 1.0;
     uint32_t extra = 0;
+    lookups = 0;
     for (int j = 0, k = 0; j < a.n_joints; ++j) {
         ArmWalkLink &L = w.link[j];
         L.off = a.off[j]; L.a = a.a[j]; L.dz = a.dz[j]; L.ca = a.ca[j]; L.sa = a.sa[j]; L.twist = a.twist[j];
@@ -157,7 +162,7 @@ ArmWalk make_arm_walk(const ArmParams &a) {
             G->t[2 * g] = a.t[k];
             if (k + 1 < a.lk_end[j]) {
                 const double half = 0.5 * std::fabs((double)a.t[k + 1] - t) * len;
-                if (half <= 0.75 * r_max) {
+                if (half <= 0.5 * reach_radii * r_max) {
                     t = 0.5 * (t + a.t[k + 1]);
                     slack = std::max(slack, half);
                     G->t[2 * g + 1] = a.t[++k];
@@ -165,6 +170,7 @@ ArmWalk make_arm_walk(const ArmParams &a) {
                 }
             }
             ++k;
+            ++lookups;
             G->tm[g] = (float)(t - 1.0);
             spread = std::max(spread, std::fabs(t) + std::fabs(t - 1.0));
         }
@@ -176,6 +182,22 @@ ArmWalk make_arm_walk(const ArmParams &a) {
     // its ends are off by at most one unit each, the sum by half of one
     const double err = (spread + 0.5) / 4.0;
     w.widen = err + 0.05 <= 1.0 ? 1 : (int)std::min(std::ceil(err + 0.05), 255.0);
+    return w;
+}
+
+// Pairs where they save at least kMinSaved lookups a state; otherwise every
+// sphere is its own group and the full check looks them up by sphere
+// (arm_hit_spheres), without a link's walk: M 8, N 1024, 16 spheres (3 saved) 369
+// us by group, 360 by sphere; 20 (8 saved) 364 and 374; 8 (none) 370 and 366;
+// 16 plans of M 6, N 512 among 60 obstacles, 8 spheres, 1145 and 1052 (two mask
+// words: the shorter queue leaves room for a block more a CU).  Vertices and lazy
+// lists take the groups either way.
+constexpr int kMinSaved = 7;
+ArmWalk make_arm_walk(const ArmParams &a) {
+    int lookups = 0;
+    ArmWalk w = group_spheres(a, 2.5, lookups);
+    if (a.n_spheres - lookups >= kMinSaved) w.by_groups = 1;
+    else w = group_spheres(a, -1.0, lookups);
     return w;
 }
 
@@ -213,8 +235,10 @@ __device__ __forceinline__ void store_params_tol_wave(const ArmParams &R, ArmPar
     for (int i = threadIdx.x; i < n; i += kWave) d[i] = i == w_tol ? __float_as_uint(sph_tol) : src[i];
 }
 
-// Word i of the walk table, the links below first_link without spheres.
-__device__ __forceinline__ uint32_t walk_word(const uint32_t *src, int i, int first_link) {
+// Word i of the walk table, the links below first_link (with the first k_first
+// spheres) without spheres.
+__device__ __forceinline__ uint32_t walk_word(const uint32_t *src, int i, int first_link, int k_first) {
+    if (i == (int)offsetof(ArmWalk, k_first) / 4) return (uint32_t)k_first;
     constexpr int per = sizeof(ArmWalkLink) / 4;
     const int L = i / per, w = i - L * per;
     const bool count = w == (int)(offsetof(ArmWalkLink, g) + offsetof(ArmGroups, n)) / 4;
@@ -239,8 +263,10 @@ __global__ void __launch_bounds__(kGridBuildThreads) k_build_grid_params(ScenePa
     } else if (threadIdx.x < kWave) {
         int first_link;
         store_params_tol_wave(R, &dst->R, S, first_link);
+        const int k_first = first_link > 0 ? R.lk_end[first_link - 1] : 0;
         for (int i = threadIdx.x; i < (int)(offsetof(ArmWalk, bin) / 4); i += kWave)
-            reinterpret_cast<uint32_t *>(&dst->W)[i] = walk_word(reinterpret_cast<const uint32_t *>(&W), i, first_link);
+            reinterpret_cast<uint32_t *>(&dst->W)[i] =
+                walk_word(reinterpret_cast<const uint32_t *>(&W), i, first_link, k_first);
     }
 }
 
@@ -388,7 +414,7 @@ __device__ __forceinline__ uint64_t list_states_limit() {
 constexpr int kListChunk = 4;
 
 template <class Model, bool UNIFORM_R, int NCH, bool LIST = false>
-__global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWords == 1 ? 6 : 5) : 4) : NCH == 1 ? 3 : NCH == 2 ? 4 : 5)
+__global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWords == 2 && arm_by_groups<Model>() ? 5 : 6) : 4) : NCH == 1 ? 3 : NCH == 2 ? 4 : 5)
     k_interior(EdgeArgs A, const ArmParams *Rg, SceneParams S) {
     constexpr int D = Model::D;
     constexpr int KP = Model::KP;
@@ -408,7 +434,8 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWo
     // the mask words in pmask, one cell's words side by side
     __shared__ typename std::conditional<GRID, GridLds<ARM ? WG : 0>, char>::type glds_raw;
     __shared__ typename std::conditional<GRID && !ARM, PointMaskLds<WG>, char>::type pmask;
-    __shared__ typename std::conditional<GRID, GridQueue<WG, ARM ? kQueueArm : kQueuePoint>[256 / kWave], char>::type gque;
+    constexpr bool GROUPS = arm_by_groups<Model>();
+    __shared__ typename std::conditional<GRID, GridQueue<WG, GROUPS ? kQueueArm : kQueuePoint>[256 / kWave], char>::type gque;
     const ObsGrid &glds = *reinterpret_cast<const ObsGrid *>(&glds_raw);  // the first grid_lds_bytes()
     for (int i = threadIdx.x; i < A.n_int; i += blockDim.x) tord[i] = A.tord[i];
     if constexpr (GRID) {  // the maps, the obstacles and the mask words this kernel reads
@@ -426,7 +453,16 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWo
     }
     __syncthreads();
     float ginv[3] = {0.f, 0.f, 0.f}, goff[3] = {0.f, 0.f, 0.f};
-    if constexpr (GRID && !ARM) {
+    if constexpr (GRID && ARM && !GROUPS) {
+        // wave-uniform and used once per link: the scales in scalar
+        // registers, the offsets in vector registers (an FMA reads one
+        // scalar operand)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            ginv[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(glds.inv[i])));
+            goff[i] = glds.off[i];
+        }
+    } else if constexpr (GRID && !ARM) {
         // point probes take both in one FMA per axis, which can read only one
         // scalar operand: vector registers avoid a copy per probe
 #pragma unroll
@@ -481,8 +517,11 @@ __global__ void __launch_bounds__(256, Model::kGrid ? (Model::kArm ? (Model::kWo
             const auto &R = *Rp;
             if constexpr (GRID) {
                 uint32_t tests = 0;
-                const bool hit =
-                    arm_hit_grid<WG, UNIFORM_R && !LIST>((ctable)Rp, q, glds.mask, glds.rec, gque[wv], tests, live);
+                bool hit;
+                if constexpr (GROUPS)
+                    hit = arm_hit_grid<WG, UNIFORM_R && !LIST>((ctable)Rp, q, glds.mask, glds.rec, gque[wv], tests, live);
+                else
+                    hit = arm_hit_spheres<WG, UNIFORM_R>((ctable)Rp, q, glds.mask, glds.rec, ginv, goff, gque[wv], tests, live);
                 n_tests += tests;
                 return hit ? -1.f : 1.f;
             } else {
@@ -1060,13 +1099,25 @@ __global__ void __launch_bounds__(256) k_state_check(ArmParams R, SceneParams S,
 // ------------------------------------------------------------------ launchers
 static int round_kp(int k) { return ((k + 7) / 8) * 8; }
 
+// The full check's interior kernel of an arm behind the bins, gw mask words.
+typedef void (*InteriorKernel)(EdgeArgs, const ArmParams *, SceneParams);
+static InteriorKernel arm_grid_kernel(int gw, bool uniform_r, bool by_groups) {
+    if (by_groups) {
+        if (gw == 1) return uniform_r ? k_interior<ArmGridModel<1>, true, 1> : k_interior<ArmGridModel<1>, false, 1>;
+        return uniform_r ? k_interior<ArmGridModel<2>, true, 1> : k_interior<ArmGridModel<2>, false, 1>;
+    }
+    if (gw == 1) return uniform_r ? k_interior<ArmSphereModel<1>, true, 1> : k_interior<ArmSphereModel<1>, false, 1>;
+    return uniform_r ? k_interior<ArmSphereModel<2>, true, 1> : k_interior<ArmSphereModel<2>, false, 1>;
+}
+
 // gw: mask words of the obstacle-bin filter (1 or 2), 0 for the chunked test
-// of every sphere against every obstacle.
+// of every sphere against every obstacle; walk: the robot's walk table (gw).
 template <int KP, int NCH>
 static hipError_t launch_arm_kp(const EdgeArgs &A, const ArmParams &R, const SceneParams &S, const EdgeBuffers &b,
                                 const gtmp_edge_opts &o, int grid_persist, hipStream_t s, const float *q0,
                                 const float *goals, const float *Q, float *verts, uint8_t *vflag, int phases,
-                                int gw) {
+                                int gw, const ArmWalk &W) {
+    const bool by_groups = W.by_groups != 0;
     const unsigned vb = (A.n_vertices + 255) / 256;
     ArmParams *Rg = reinterpret_cast<ArmParams *>(static_cast<char *>(b.workspace) + A.off_params);
     float r_max = 0.f;
@@ -1074,7 +1125,6 @@ static hipError_t launch_arm_kp(const EdgeArgs &A, const ArmParams &R, const Sce
     ObsGrid *grid = const_cast<ObsGrid *>(A.grid);
     if (phases & kPhaseVertices) {
         if (gw) {
-            const ArmWalk W = make_arm_walk(R);
             // the bins serve the vertex flags and, later, the interior kernel
             // (which also reads the robot table written beside them)
             hipLaunchKernelGGL(k_build_grid_params, dim3(2), dim3(kGridBuildThreads), 0, s, S,
@@ -1126,14 +1176,7 @@ static hipError_t launch_arm_kp(const EdgeArgs &A, const ArmParams &R, const Sce
     } else if (gw) {
         // robots whose spheres share one radius read the exact test's starting
         // gap from the obstacle records
-        if (gw == 1 && R.uniform_r)
-            hipLaunchKernelGGL((k_interior<ArmGridModel<1>, true, 1>), dim3(grid_persist), dim3(256), 0, s, A, Rg, S);
-        else if (gw == 1)
-            hipLaunchKernelGGL((k_interior<ArmGridModel<1>, false, 1>), dim3(grid_persist), dim3(256), 0, s, A, Rg, S);
-        else if (R.uniform_r)
-            hipLaunchKernelGGL((k_interior<ArmGridModel<2>, true, 1>), dim3(grid_persist), dim3(256), 0, s, A, Rg, S);
-        else
-            hipLaunchKernelGGL((k_interior<ArmGridModel<2>, false, 1>), dim3(grid_persist), dim3(256), 0, s, A, Rg, S);
+        hipLaunchKernelGGL(arm_grid_kernel(gw, R.uniform_r, by_groups), dim3(grid_persist), dim3(256), 0, s, A, Rg, S);
     } else if (R.uniform_r) {
         hipLaunchKernelGGL((k_interior<ArmModel<KP>, true, NCH>), dim3(grid_persist), dim3(256), 0, s, A, Rg, S);
     } else {
@@ -1321,10 +1364,11 @@ hipError_t launch_edge_phases(const EdgePlan &plan, const ArmParams *arm, const 
         const int gw = o.sphere_chunks == 0 && n_obs <= kGridArmMaxObs ? grid_words(n_obs) : 0;
         const int nch = o.sphere_chunks == 1 ? 1 : o.sphere_chunks == 4 ? 4 : 2;
         A.grid = reinterpret_cast<const ObsGrid *>(ws + plan.off_grid);
+        ArmWalk W{};
+        if (gw) W = make_arm_walk(R);
         const void *kern = nullptr;
         switch (gw ? -gw : kp * 8 + nch) {
-            case -1: kern = R.uniform_r ? (const void *)k_interior<ArmGridModel<1>, true, 1> : (const void *)k_interior<ArmGridModel<1>, false, 1>; break;
-            case -2: kern = R.uniform_r ? (const void *)k_interior<ArmGridModel<2>, true, 1> : (const void *)k_interior<ArmGridModel<2>, false, 1>; break;
+            case -1: case -2: kern = (const void *)arm_grid_kernel(gw, R.uniform_r, W.by_groups != 0); break;
 #define GTMP_KK(K, C) case K * 8 + C: kern = R.uniform_r ? (const void *)k_interior<ArmModel<K>, true, C> : (const void *)k_interior<ArmModel<K>, false, C>; break;
 #define GTMP_KK3(K) GTMP_KK(K, 1) GTMP_KK(K, 2) GTMP_KK(K, 4)
             GTMP_KK3(8) GTMP_KK3(16) GTMP_KK3(24) GTMP_KK3(32) GTMP_KK3(40) GTMP_KK3(48) GTMP_KK3(56) GTMP_KK3(64)
@@ -1335,7 +1379,7 @@ hipError_t launch_edge_phases(const EdgePlan &plan, const ArmParams *arm, const 
         const int grid = persistent_grid(kern, 256, o.blocks_per_cu, plan.n_tiles);
         A.wstats = wave_stat_slots(A, (unsigned)grid);
         switch (kp * 8 + nch) {
-#define GTMP_LA(K, C) case K * 8 + C: return launch_arm_kp<K, C>(A, R, scene, b, o, grid, s, b.q0, b.goals, b.Q, verts, vflag, phases, gw);
+#define GTMP_LA(K, C) case K * 8 + C: return launch_arm_kp<K, C>(A, R, scene, b, o, grid, s, b.q0, b.goals, b.Q, verts, vflag, phases, gw, W);
 #define GTMP_LA3(K) GTMP_LA(K, 1) GTMP_LA(K, 2) GTMP_LA(K, 4)
             GTMP_LA3(8) GTMP_LA3(16) GTMP_LA3(24) GTMP_LA3(32) GTMP_LA3(40) GTMP_LA3(48) GTMP_LA3(56) GTMP_LA3(64)
 #undef GTMP_LA3

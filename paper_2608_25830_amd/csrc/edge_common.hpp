@@ -329,7 +329,7 @@ template <int WORDS, int CAP>
 struct GridQueue {
     // one array per field: the centre with the first mask word beside it in
     // one 16-byte entry (one store per probe)
-    static constexpr int kWords = WORDS;
+    static constexpr int kWords = WORDS, kCap = CAP;
     float4 c[CAP];                                                // centre x, y, z; mask word 0 (bits)
     uint32_t m[WORDS > 1 ? WORDS - 1 : 1][WORDS > 1 ? CAP : 1];  // mask words 1 ..
     uint16_t own[CAP];                                            // owning lane | probe index << 8
@@ -445,15 +445,15 @@ struct GridProber {
             const uint32_t n = (uint32_t)__popcll(wmask);
             if (__builtin_amdgcn_inverse_ballot_w64(wmask)) push(rank_in(wmask), n);  // any != 0 && hit == 0 in this lane
             tail += n * per;
-        }
-    }
-
-    // Tests the waiting entries 64 at a time; after each offer (of up to two
-    // entries a lane).
-    __device__ __forceinline__ void drain_full() {
-        while (tail >= (uint32_t)kWave) {
-            tail -= (uint32_t)kWave;
-            drain(tail, kWave);
+            if constexpr (Queue::kCap > kQueuePoint) {  // up to two entries a lane: twice at most
+                while (tail >= (uint32_t)kWave) {
+                    tail -= (uint32_t)kWave;
+                    drain(tail, kWave);
+                }
+            } else if (tail >= (uint32_t)kWave) {
+                tail -= (uint32_t)kWave;
+                drain(tail, kWave);
+            }
         }
     }
 
@@ -503,30 +503,43 @@ __device__ __forceinline__ uint32_t arm_mask_word(const uint32_t *cells, float v
 // contact with a sphere of the group.  The centres themselves, fma(t, p - b, b)
 // as the full test forms them, are formed only for the groups queued for an
 // exact test.
-// Bound by vector issue (nine tenths of the cycles at six waves a SIMD).  M 8,
-// N 2048, 32.3 M states: a lookup per sphere, its parameters in 118 scalar
-// loads a state, took 1.20 ms; groups alone cut a sixth of the vector
-// instructions and no time (1.19 ms: the waves waited for those loads); two
-// vector loads a link and the next group's words requested before the current
-// group is worked on, 1.085 ms.  Requesting a link's parameters one link ahead
+// Bound by instruction issue.  M 8, N 2048, 32.3 M states: a lookup per sphere,
+// its parameters in 118 scalar loads a state, took 1.20 ms; groups alone cut a
+// sixth of the vector instructions and no time (1.19 ms: the waves waited for
+// those loads); three vector-wide scalar loads a link and the next group's words
+// requested before the current group is worked on, 1.085 ms; the bin offsets held
+// in vector registers (an FMA reads one scalar operand) and a group's parameters
+// shifted as 64-bit words, 1.05.  Requesting a link's parameters one link ahead
 // or seven waves a SIMD measured the same; a link's groups looked up all at
-// once spills (2.7 ms).
+// once spills (2.7 ms).  Two mask words take 96 registers and a queue of 192
+// entries, which leaves five waves a SIMD; M 8, N 1024 among 48 obstacles 750 us
+// (a lookup per sphere at six waves: 916).
 // The link being walked: its joint, its groups and the bin maps.
 struct ArmWalker {
     ctable T;
-    u32x8 head, bin;
+    u32x8 head;
+    u32x4 bin;
     u32x16 body;
+    typedef const __attribute__((address_space(4))) u32x4 *c4;
     typedef const __attribute__((address_space(4))) u32x8 *c8;
     typedef const __attribute__((address_space(4))) u32x16 *c16;
     __device__ __forceinline__ explicit ArmWalker(ctable t) : T(t) {}
 };
-__device__ __forceinline__ JointP joint_of(ArmWalker &A, int j) {
+struct WalkJoint {
+    u32x8 h;
+    __device__ __forceinline__ float off() const { return __uint_as_float(h[0]); }
+    __device__ __forceinline__ float a() const { return __uint_as_float(h[1]); }
+    __device__ __forceinline__ float dz() const { return __uint_as_float(h[2]); }
+    __device__ __forceinline__ float ca() const { return __uint_as_float(h[3]); }
+    __device__ __forceinline__ float sa() const { return __uint_as_float(h[4]); }
+    __device__ __forceinline__ int twist() const { return (int)h[5]; }
+};
+__device__ __forceinline__ WalkJoint joint_of(ArmWalker &A, int j) {
     asm volatile("" : "+s"(A.T));  // the maps are read again for each link rather than held (and spilled)
     A.head = *(ArmWalker::c8)&A.T->W.link[j];
     A.body = *(ArmWalker::c16)&A.T->W.link[j].g;
-    A.bin = *(ArmWalker::c8)A.T->W.bin;
-    return JointP{__uint_as_float(A.head[0]), __uint_as_float(A.head[1]), __uint_as_float(A.head[2]),
-                  __uint_as_float(A.head[3]), __uint_as_float(A.head[4]), (int)A.head[5]};
+    A.bin = *(ArmWalker::c4)A.T->W.bin;
+    return WalkJoint{A.head};
 }
 
 template <int WORDS, bool UNI = false>
@@ -537,12 +550,17 @@ __device__ __forceinline__ bool arm_hit_grid(ctable T, const float (&q)[GTMP_MAX
     const auto rad = [&](uint32_t k) { return T->R.r[k]; };
     GridProber<ArmQueue<WORDS>, UNI, decltype(rad)> P(Qw, rec, tests, rad, live);
     ArmWalker walk(T);
-    float fb[3] = {T->W.bin[4], T->W.bin[5], T->W.bin[6]};  // o_0 = 0
+    float off[3], fb[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        off[i] = to_vgpr(T->W.bin[4 + i]);
+        fb[i] = off[i];  // o_0 = 0
+    }
     arm_fk_visit<GTMP_MAX_JOINTS>(walk, T->R.n_joints, q, [&](int, const float (&b)[3], const float (&p)[3]) {
         float fp[3], fd[3], d[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            fp[i] = __builtin_fmaf(p[i], __uint_as_float(walk.bin[i]), __uint_as_float(walk.bin[4 + i]));
+            fp[i] = __builtin_fmaf(p[i], __uint_as_float(walk.bin[i]), off[i]);
             fd[i] = fp[i] - fb[i];
             d[i] = p[i] - b[i];
             // formed once per link: kept in registers rather than re-formed
@@ -566,7 +584,9 @@ __device__ __forceinline__ bool arm_hit_grid(ctable T, const float (&q)[GTMP_MAX
             for (int wd = 0; wd < WORDS; ++wd) mw[wd] = first[wd][0] & first[wd][1] & first[wd][2];
             uint32_t k = g[12], bits = pairs;
             uint32_t tm1 = g[1], tm2 = g[2], tm3 = g[3];
-            uint32_t t0 = g[4], t1 = g[5], t2 = g[6], t3 = g[7], t4 = g[8], t5 = g[9], t6 = g[10], t7 = g[11];
+            typedef unsigned long long ull;
+            ull tt0 = g[4] | (ull)g[5] << 32, tt1 = g[6] | (ull)g[7] << 32, tt2 = g[8] | (ull)g[9] << 32,
+                tt3 = g[10] | (ull)g[11] << 32;
             // one copy of the probe and of the drain for the link's groups:
             // the words of the next group are requested before the current
             // ones are worked on, and its parameters shifted down
@@ -578,22 +598,21 @@ __device__ __forceinline__ bool arm_hit_grid(ctable T, const float (&q)[GTMP_MAX
                 P.offer(mw, per, [&](int r, uint32_t lanes) {
                     float c[3];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(__uint_as_float(t0), d[i], b[i]);
+                    for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(__uint_as_float((uint32_t)tt0), d[i], b[i]);
                     P.entry(r, mw, c, k);
                     if (per == 2) {
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(__uint_as_float(t1), d[i], b[i]);
+                        for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(__uint_as_float((uint32_t)(tt0 >> 32)), d[i], b[i]);
                         P.entry(r + (int)lanes, mw, c, k + 1);
                     }
                 });
-                P.drain_full();
-                if (--left == 0) break;
+                    if (--left == 0) break;
 #pragma unroll
                 for (int wd = 0; wd < WORDS; ++wd) mw[wd] = raw[wd][0] & raw[wd][1] & raw[wd][2];
                 k += per;
                 bits >>= 1;
                 tm1 = tm2; tm2 = tm3;
-                t0 = t2; t1 = t3; t2 = t4; t3 = t5; t4 = t6; t5 = t7;
+                tt0 = tt1; tt1 = tt2; tt2 = tt3;
             }
         };
         groups(walk.body);
@@ -601,6 +620,51 @@ __device__ __forceinline__ bool arm_hit_grid(ctable T, const float (&q)[GTMP_MAX
             typedef const __attribute__((address_space(4))) u32x16 *c16;
             const u32x16 g = *(c16)&T->W.extra[x];
             groups(g);
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) fb[i] = fp[i];
+    });
+    return P.finish();
+}
+
+// The same with a lookup per sphere, its parameters read as it comes up (inv, off:
+// the bins' own maps).  For arms of few spheres, or spheres too far apart to share
+// lookups, where a link's walk takes more than the lookups it saves; make_arm_walk
+// has the measurements and draws the line.
+template <int WORDS, bool UNI, class Queue>
+__device__ __forceinline__ bool arm_hit_spheres(ctable T, const float (&q)[GTMP_MAX_JOINTS], const GridMaskTable *mk,
+                                                const float4 (*rec)[2], const float (&inv)[3], const float (&off)[3],
+                                                Queue &Qw, uint32_t &tests, bool live) {
+    const auto &R = T->R;
+    const auto rad = [&](uint32_t k) { return R.r[k]; };
+    GridProber<Queue, UNI, decltype(rad)> P(Qw, rec, tests, rad, live);
+    float fb[3] = {off[0], off[1], off[2]};  // o_0 = 0
+    const int kf = T->W.k_first;
+    arm_fk_visit<GTMP_MAX_JOINTS>(R, R.n_joints, q, [&](int L, const float (&b)[3], const float (&p)[3]) {
+        float fp[3], fd[3], d[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            fp[i] = __builtin_fmaf(p[i], inv[i], off[i]);
+            fd[i] = fp[i] - fb[i];
+            d[i] = p[i] - b[i];
+            asm volatile("" : "+v"(fp[i]), "+v"(fd[i]), "+v"(d[i]));
+        }
+        const int kl = L == 1 ? 0 : R.lk_end[L - 2];
+        const uint32_t k0 = (uint32_t)(kl > kf ? kl : kf), k1 = (uint32_t)R.lk_end[L - 1];
+        for (uint32_t k = k0; k < k1; ++k) {  // unsigned: the parameter address is a plain increment
+            const float tm = T->W.tm1[k];
+            uint32_t bin[3], mw[WORDS];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) bin[i] = grid_bin(__builtin_fmaf(tm, fd[i], fp[i]));
+#pragma unroll
+            for (int wd = 0; wd < WORDS; ++wd) mw[wd] = mk[wd][0][bin[0]] & mk[wd][1][bin[1]] & mk[wd][2][bin[2]];
+            P.offer(mw, 1u, [&](int r, uint32_t) {
+                const float t = R.t[k];
+                float c[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) c[i] = __builtin_fmaf(t, d[i], b[i]);
+                P.entry(r, mw, c, k);
+            });
         }
 #pragma unroll
         for (int i = 0; i < 3; ++i) fb[i] = fp[i];
@@ -636,7 +700,6 @@ __device__ __forceinline__ bool point_hit_grid_by(const float (&p)[W][SP], const
 #pragma unroll
         for (int i = 0; i < W; ++i) and_mask(i, bin[i], mw);
         P.offer(mw, 1u, [&](int r, uint32_t) { P.entry(r, mw, c, 0u); });
-        P.drain_full();
     }
     return P.finish();
 }
@@ -1049,7 +1112,18 @@ struct ArmGridModel {
     static constexpr int kWords = WORDS;
     static constexpr int D = GTMP_MAX_JOINTS;
     static constexpr int KP = 1;
+    static constexpr bool kGroups = true;
 };
+// The same with a lookup per sphere (arm_hit_spheres).
+template <int WORDS>
+struct ArmSphereModel : ArmGridModel<WORDS> {
+    static constexpr bool kGroups = false;
+};
+template <class Model>
+constexpr bool arm_by_groups() {
+    if constexpr (Model::kArm && Model::kGrid) return Model::kGroups;
+    else return false;
+}
 
 // Point states in R^W tested through the obstacle bins, S states per
 // evaluation (WORDS mask words).

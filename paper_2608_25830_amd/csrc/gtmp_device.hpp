@@ -65,7 +65,7 @@ struct ArmParams {
 };
 
 // What the bin-filtered arm test reads per link, packed so that a link takes two
-// scalar loads (make_arm_walk): the joint, and up to four groups of one or two
+// wide scalar loads beside the bin maps' (make_arm_walk): the joint, and up to four groups of one or two
 // neighbouring spheres looked up together.  Groups past the fourth of a link
 // lie in extra[x_begin .. x_end).
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
@@ -88,9 +88,12 @@ struct alignas(64) ArmWalkLink {
 struct alignas(64) ArmWalk {
     ArmWalkLink link[GTMP_MAX_JOINTS];
     ArmGroups extra[GTMP_MAX_ROBOT_SPHERES / 4];
+    float tm1[GTMP_MAX_ROBOT_SPHERES];  // lookups by sphere: its fraction along the link, less 1
     float slack;   // bound on the distance of a sphere's centre from its group's, rounded up
     int widen;     // bins an obstacle's interval is widened by on each side
-    uint32_t pad[6];
+    int by_groups;  // whether the full check looks spheres up by group (make_arm_walk)
+    int k_first;    // lookups by sphere: those below it reach no obstacle (set on the device)
+    uint32_t pad[4];
     float bin[8];  // bin maps (scale on the three axes, 0, offset, 0), written by the kernel that builds the bins
 };
 static_assert(offsetof(ArmWalk, bin) % 32 == 0, "read as one 8-word vector");
@@ -378,13 +381,22 @@ __device__ __forceinline__ void joint_sincos(float x, float &s, float &c) {
 // ---------------------------------------------------------------------------
 typedef float v32f __attribute__((ext_vector_type(32)));
 
-struct JointP {
-    float off, a, dz, ca, sa;
-    int twist;
+// Joint j of a robot table, each parameter read where it is used (all of them
+// ahead of the joint's sine cost the arm of eight spheres 1 % of its check).
+template <class AP>
+struct JointRef {
+    const AP &A;
+    int j;
+    __device__ __forceinline__ float off() const { return A.off[j]; }
+    __device__ __forceinline__ float a() const { return A.a[j]; }
+    __device__ __forceinline__ float dz() const { return A.dz[j]; }
+    __device__ __forceinline__ float ca() const { return A.ca[j]; }
+    __device__ __forceinline__ float sa() const { return A.sa[j]; }
+    __device__ __forceinline__ int twist() const { return A.twist[j]; }
 };
 template <class AP>
-__device__ __forceinline__ JointP joint_of(const AP &A, int j) {
-    return JointP{A.off[j], A.a[j], A.dz[j], A.ca[j], A.sa[j], A.twist[j]};
+__device__ __forceinline__ JointRef<AP> joint_of(const AP &A, int j) {
+    return JointRef<AP>{A, j};
 }
 
 // u v + x y and u v - x y of the kinematics, in the edge checks with the product
@@ -418,26 +430,26 @@ __device__ __forceinline__ void arm_fk_visit(AP &A, int n_joints, const float (&
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         if (j >= n_joints) break;
-        const JointP J = joint_of(A, j);
+        const auto J = joint_of(A, j);
         const float b[3] = {p0, p1, p2};
         float st, ct;
-        joint_sincos(q[j] + J.off, st, ct);
-        const float ca = J.ca, sa = J.sa;
+        joint_sincos(q[j] + J.off(), st, ct);
+        const float ca = J.ca(), sa = J.sa();
         if (j == 0) {
             x0 = ct; x1 = st; x2 = 0.f;
-            p0 = J.a * ct; p1 = J.a * st; p2 = J.dz;
+            p0 = J.a() * ct; p1 = J.a() * st; p2 = J.dz();
             y0 = -(ca * st); y1 = ca * ct; y2 = sa;
             z0 = sa * st; z1 = -(sa * ct); z2 = ca;
         } else {
             const float xn0 = fk_last(ct, x0, st, y0), xn1 = fk_last(ct, x1, st, y1), xn2 = fk_last(ct, x2, st, y2);
-            p0 += fk_first(J.a, xn0, J.dz, z0);
-            p1 += fk_first(J.a, xn1, J.dz, z1);
-            p2 += fk_first(J.a, xn2, J.dz, z2);
+            p0 += fk_first(J.a(), xn0, J.dz(), z0);
+            p1 += fk_first(J.a(), xn1, J.dz(), z1);
+            p2 += fk_first(J.a(), xn2, J.dz(), z2);
             {
                 const float yp0 = fk_diff(ct, y0, st, x0), yp1 = fk_diff(ct, y1, st, x1), yp2 = fk_diff(ct, y2, st, x2);
                 // y' = ca yp + sa z, z' = ca z - sa yp; exact quarter turns and
                 // no twist give the same values without the products
-                const int tw = J.twist;
+                const int tw = J.twist();
                 if (tw == kTwistNone) {
                     y0 = yp0; y1 = yp1; y2 = yp2;
                 } else if (tw == kTwistPlus) {
