@@ -142,7 +142,7 @@ static ArmWalk group_spheres(const ArmParams &a, double reach_radii, int &lookup
         r_max = std::max(r_max, a.r[k]);
         w.tm1[k] = a.t[k] - 1.f;
     }
-    double slack = 0.0, spread = 1.0;
+    double slack = 0.0, spread = 1.0, tm_max = 1.0;
     uint32_t extra = 0;
     lookups = 0;
     for (int j = 0, k = 0; j < a.n_joints; ++j) {
@@ -173,15 +173,23 @@ static ArmWalk group_spheres(const ArmParams &a, double reach_radii, int &lookup
             ++lookups;
             G->tm[g] = (float)(t - 1.0);
             spread = std::max(spread, std::fabs(t) + std::fabs(t - 1.0));
+            tm_max = std::max(tm_max, std::fabs(t - 1.0));
         }
         L.x_end = extra;
     }
     // rounded up, with room for the FP32 centres (1e-5 of the arm's reach)
     w.slack = slack > 0.0 ? (float)(slack * (1.0 + 1e-6) + 1e-5 * a.reach) : 0.f;
-    // a probe's bin coordinate is a quarter bin per unit in the last place:
-    // its ends are off by at most one unit each, the sum by half of one
-    const double err = (spread + 0.5) / 4.0;
-    w.widen = err + 0.05 <= 1.0 ? 1 : (int)std::min(std::ceil(err + 0.05), 255.0);
+    // How far, in quarters of a bin, a lookup may be from the bin of the FP32
+    // centre.  Values below 2^24 are whole quarters: half of one for the rounded
+    // offset, for each end (weighted |t| and |t - 1|) and for the sum.  Ends as
+    // far from the bins as the arm reaches, 2^13 spans at most and fewer for
+    // thicker spheres (a scene spans two radii), have another half each, and
+    // there the rounding of t - 1, of the ends' difference and of the centre
+    // itself count: at 2^13 spans one, |t - 1| and one quarter.  (The bound is
+    // about twice the largest error found; a bin of widening is four quarters.)
+    const double spans = r_max > 0.f ? std::min(8192.0, 0.5 * (double)a.reach / r_max) / 8192.0 : 1.0;
+    const double err = (1.0 + 0.5 * spread + spans * (2.5 + 0.5 * spread + tm_max)) / 4.0;
+    w.widen = (int)std::min(std::max(std::ceil(err), 1.0), 255.0);
     return w;
 }
 

@@ -174,7 +174,8 @@ constexpr int kGridBuildThreads = 3 * kGridCells;  // one (axis, bin) cell per t
 // at a point up to `slack` away (arms: a pair of spheres by its middle), the
 // obstacles' intervals widened by `widen` bins, and a probe region of radius
 // `reach` around the origin (0: unknown) over which bin coordinates stay below
-// 2^21, where the arms' lookups are exact to a quarter of a bin.
+// 2^22 (the bins of a scene within reach span at least 2^-13 of it), where the
+// arms' lookups are exact to a bin.
 struct GridBuild {
     float r_max, slack, reach;
     int widen;
@@ -246,6 +247,9 @@ __device__ __forceinline__ void build_grid_block(const SceneParams &S, int wdim,
         constexpr float kSpan = (float)(kGridCells - 3);
         const float scale = __builtin_fmaxf(1.f, __builtin_fmaxf(__builtin_fabsf(a), __builtin_fabsf(b)));
         const float span = __builtin_fmaxf(b - a, __builtin_fmaxf(1e-6f * scale, 0x1p-13f * B.reach));
+        const float grow = __builtin_fmaxf(0.5f * (span - (b - a)), 0.f);  // a scene smaller than that
+        a -= grow;
+        b += grow;
         const float pad = span * (4.f / kSpan);
         a -= pad;
         b += pad;
@@ -497,8 +501,8 @@ __device__ __forceinline__ uint32_t arm_mask_word(const uint32_t *cells, float v
 // neighbours of a link, ArmWalk): the value of a group's middle b + t (p - b)
 // on axis i is taken as fp_i + (t - 1) (fp_i - fb_i), fb and fp the values of
 // the link's ends (o_{L-1} and o_L, each formed once: o_L's serves as the next
-// link's fb), each within one quarter of a bin; the obstacles' intervals are
-// widened to cover the middle's distance from its spheres and that error
+// link's fb), each within half a quarter of a bin (a quarter for the ends
+// farthest from the bins); the obstacles' intervals are widened to cover the middle's distance from its spheres and that error
 // (make_arm_walk), so the bins list every obstacle the exact test can find in
 // contact with a sphere of the group.  The centres themselves, fma(t, p - b, b)
 // as the full test forms them, are formed only for the groups queued for an
