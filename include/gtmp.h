@@ -628,12 +628,12 @@ gtmp_status gtmp_surrogate_layout(int32_t offsets[11]);
 /* params_bf16 <- bf16(params) (after the caller writes new FP32 values). */
 gtmp_status gtmp_surrogate_refresh_bf16(const gtmp_surrogate *net, void *stream);
 
-/* Workspace for gtmp_surrogate_grad with a batch of n rows, and for the
- * inference calls processing up to n rows per chunk. */
+/* Workspace for gtmp_surrogate_grad with a batch of n rows; any such workspace
+ * serves gtmp_surrogate_infer for any number of rows. */
 gtmp_status gtmp_surrogate_workspace_size(int64_t n, size_t *bytes);
 
 /* Logits of n configurations X [n][d] (device) -> logits [n] (device).
- * Any n >= 0; processed in chunks that fit the workspace. */
+ * Any n >= 0; the workspace holds the weights in the kernel's order. */
 gtmp_status gtmp_surrogate_infer(const gtmp_surrogate *net, int64_t n, const float *X, float *logits,
                                  void *workspace, size_t ws_bytes, void *stream);
 

@@ -388,13 +388,11 @@ ExpandPlan make_expand_plan(const gtmp_problem &p, bool bias) {
     e.off_rankws = o; o = up256(o + rp.total);
     if (bias) {
         const uint64_t K = (uint64_t)kBiasCandidates * Nn;
-        e.bias_rows = K;
         e.off_bX = o; o = up256(o + sizeof(float) * K * p.d);
         e.off_bz = o; o = up256(o + sizeof(float) * K);
         e.off_bfree = o; o = up256(o + sizeof(uint32_t) * K);
         e.off_bcount = o; o = up256(o + 64);
-        e.bws_bytes = sur_infer_bytes((int64_t)((K + 255) / 256 * 256));
-        e.off_bws = o; o = up256(o + e.bws_bytes);
+        e.off_bws = o; o = up256(o + sur_infer_bytes());
     }
     e.total = o;
     return e;
@@ -447,7 +445,7 @@ hipError_t launch_expand(const gtmp_problem &p, const float *q0, const float *go
             uint32_t *bcount = reinterpret_cast<uint32_t *>(ws + e.off_bcount);
             hipLaunchKernelGGL(k_bias_midpoints, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s, d, K, sorted, nv, U,
                                Vv, bX);
-            hipError_t err = launch_sur_infer(*bias, (int64_t)K, bX, bz, ws + e.off_bws, e.bws_bytes, s);
+            hipError_t err = launch_sur_infer(*bias, (int64_t)K, bX, bz, ws + e.off_bws, s);
             if (err != hipSuccess) return err;
             hipLaunchKernelGGL(k_bias_compact, dim3(1), dim3(1024), 0, s, K, bz, bias_tau, sorted, bfree, bcount);
             sorted = bfree;

@@ -752,9 +752,9 @@ gtmp_status gtmp_surrogate_infer(const gtmp_surrogate *net, int64_t n, const flo
     if (n < 0) return fail(GTMP_EINVAL, "n=%lld < 0", (long long)n);
     if (n == 0) return GTMP_OK;
     if (!X || !logits) return fail(GTMP_EINVAL, "NULL buffer");
-    st = check_ws(workspace, ws_bytes, gtmp::sur_infer_bytes(256));
+    st = check_ws(workspace, ws_bytes, gtmp::sur_infer_bytes());
     if (st != GTMP_OK) return st;
-    return hip_status(gtmp::launch_sur_infer(sn, n, X, logits, workspace, ws_bytes, (hipStream_t)stream),
+    return hip_status(gtmp::launch_sur_infer(sn, n, X, logits, workspace, (hipStream_t)stream),
                       "gtmp_surrogate_infer");
 }
 

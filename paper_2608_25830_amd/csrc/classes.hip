@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(kArchiveThreads) k_class_archive(int M, int N,
         const uint64_t b = ballot(fresh);
         const int s = na0 + rank_in(b), total = __popcll(b);
         if (fresh) slot_s[lane] = s < cap ? s : -2;
-        const int room = cap - na0 < total ? cap - na0 : total;
+        const int left = cap > na0 ? cap - na0 : 0, room = left < total ? left : total;
         if (lane == 0) {
             *a_count = na0 + room;
             if (total > room) atomicAdd(overflow, (uint32_t)(total - room));

@@ -88,8 +88,7 @@ struct ExpandPlan {
     uint32_t max_k;  // closest pairs ranked per layer at most
     size_t off_informed, off_rank, off_sorted, off_rankws;
     // surrogate-biased heuristic half (when planned with bias)
-    uint64_t bias_rows;
-    size_t off_bX, off_bz, off_bfree, off_bcount, off_bws, bws_bytes;
+    size_t off_bX, off_bz, off_bfree, off_bcount, off_bws;
     size_t total;
 };
 // One growing plan's expansion inside a batch: the arguments of

@@ -981,13 +981,6 @@ __global__ void __launch_bounds__(256) k_label_states(int d, int64_t n, int H, u
 // ------------------------------------------------------------------ host side
 static unsigned blocks_for(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
 
-// Workspace carve-up of the inference calls.
-struct SurWs {
-    uint4 *Wf;  // fragment-order weights
-    uint16_t *X0, *A[4];
-    float *logit_tmp, *Xf;
-    size_t total;
-};
 static size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace of a training step of n rows (a multiple of 256).
@@ -1009,56 +1002,26 @@ static TrainBufs carve_train(int64_t n, void *base) {
     return w;
 }
 
-// Inference needs the fragment-order weights, and for chunked use the
-// features, two activation buffers (layers alternate between them), the
-// logits and the FP32 probe states.
-static SurWs carve_infer(int64_t n, void *base) {
-    SurWs w{};
-    char *p = static_cast<char *>(base);
-    size_t o = 0;
-    auto take = [&](size_t bytes) { char *q = p ? p + o : nullptr; o = up256(o + bytes); return q; };
-    w.Wf = reinterpret_cast<uint4 *>(take(sizeof(uint4) * kFragTotal));
-    w.X0 = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * GTMP_SUR_IN));
-    w.A[0] = w.A[2] = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * GTMP_SUR_WIDTH));
-    w.A[1] = w.A[3] = reinterpret_cast<uint16_t *>(take(sizeof(uint16_t) * n * GTMP_SUR_WIDTH));
-    w.logit_tmp = reinterpret_cast<float *>(take(sizeof(float) * n));
-    w.Xf = reinterpret_cast<float *>(take(sizeof(float) * n * GTMP_MAX_DOF));
-    w.total = o;
-    return w;
-}
-
 size_t sur_workspace_bytes(int64_t n) { return carve_train(n, nullptr).total; }
 
-int64_t sur_rows_for(size_t bytes) {
-    // largest multiple of 256 rows whose inference carve-up fits
-    int64_t lo = 0, hi = 1 << 24;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) / 2;
-        if (carve_infer(mid * 256, nullptr).total <= bytes) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo * 256;
-}
-
-size_t sur_infer_bytes(int64_t n) { return carve_infer(n, nullptr).total; }
+// Inference keeps its activations in LDS: the weights in fragment order.
+size_t sur_infer_bytes() { return up256(sizeof(uint4) * kFragTotal); }
 
 static void weight_frag(const SurNet &net, uint4 *Wf, hipStream_t s) {
     hipLaunchKernelGGL(k_weight_frag, dim3((kFragTotal + 255) / 256), dim3(256), 0, s, net.d, net.p16, sur_layout(),
                        Wf);
 }
 
-hipError_t launch_sur_infer(const SurNet &net, int64_t n, const float *X, float *logits, void *ws, size_t ws_bytes,
-                            hipStream_t s) {
-    (void)ws_bytes;
+hipError_t launch_sur_infer(const SurNet &net, int64_t n, const float *X, float *logits, void *ws, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const SurWs w = carve_infer(0, ws);
-    weight_frag(net, w.Wf, s);
+    uint4 *Wf = static_cast<uint4 *>(ws);
+    weight_frag(net, Wf, s);
     // chunks bound the grid size
     constexpr int64_t kChunk = (int64_t)1 << 30;
     for (int64_t r = 0; r < n; r += kChunk) {
         const int64_t c = n - r < kChunk ? n - r : kChunk;
         hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)((c + kFR - 1) / kFR)), dim3(256), 0, s, net.d, c,
-                           X + r * net.d, net.fourier, reinterpret_cast<const bf16x8 *>(w.Wf), net.p16, net.p32,
+                           X + r * net.d, net.fourier, reinterpret_cast<const bf16x8 *>(Wf), net.p16, net.p32,
                            sur_layout(), logits + r);
     }
     return hipGetLastError();

@@ -28,11 +28,9 @@ struct SurBox {
 };
 
 size_t sur_workspace_bytes(int64_t n);
-int64_t sur_rows_for(size_t bytes);  // rows per inference chunk that fit `bytes`
-size_t sur_infer_bytes(int64_t n);   // inference workspace for n rows per chunk
+size_t sur_infer_bytes();            // workspace of an inference call, any number of rows
 
-hipError_t launch_sur_infer(const SurNet &net, int64_t n, const float *X, float *logits, void *ws, size_t ws_bytes,
-                            hipStream_t s);
+hipError_t launch_sur_infer(const SurNet &net, int64_t n, const float *X, float *logits, void *ws, hipStream_t s);
 hipError_t launch_sur_grad(const SurNet &net, int n, const float *X, const uint8_t *y, float *grad, float *loss,
                            float *logits, void *ws, hipStream_t s);
 hipError_t launch_sur_adam(const SurNet &net, const float *grad, float *m, float *v, int t, float lr, float b1,
