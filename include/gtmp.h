@@ -278,7 +278,11 @@ typedef struct gtmp_rrtc_opts {
     float ell_factor;    /* >= 1: major axis of the query ellipsoid over |y - x| */
     int32_t reserved;
     unsigned long long *stats; /* optional device [6]: calls, successes, iterations, tree nodes, states
-                                  checked, nearest-node distances evaluated.  Added to. */
+                                  checked, nearest-node distances evaluated.  Added to.  States checked:
+                                  all of a free segment's; of one in contact, those up to the end of the
+                                  round the contact lies in (64 states for an arm among at most 96
+                                  obstacles, otherwise the least power of two that holds the segment, up
+                                  to 64).  The kernel may evaluate fewer. */
 } gtmp_rrtc_opts;
 
 /* Bytes of device workspace gtmp_rrtc_repair needs for this problem. */

@@ -502,9 +502,10 @@ __device__ __forceinline__ uint32_t arm_mask_word(const uint32_t *cells, float v
 // on axis i is taken as fp_i + (t - 1) (fp_i - fb_i), fb and fp the values of
 // the link's ends (o_{L-1} and o_L, each formed once: o_L's serves as the next
 // link's fb), each within half a quarter of a bin (a quarter for the ends
-// farthest from the bins); the obstacles' intervals are widened to cover the middle's distance from its spheres and that error
-// (make_arm_walk), so the bins list every obstacle the exact test can find in
-// contact with a sphere of the group.  The centres themselves, fma(t, p - b, b)
+// farthest from the bins); the obstacles' intervals are widened to cover the
+// middle's distance from its spheres and that error (make_arm_walk), so the
+// bins list every obstacle the exact test can find in contact with a sphere of
+// the group.  The centres themselves, fma(t, p - b, b)
 // as the full test forms them, are formed only for the groups queued for an
 // exact test.
 // Bound by instruction issue.  M 8, N 2048, 32.3 M states: a lookup per sphere,

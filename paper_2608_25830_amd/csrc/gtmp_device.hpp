@@ -65,9 +65,9 @@ struct ArmParams {
 };
 
 // What the bin-filtered arm test reads per link, packed so that a link takes two
-// wide scalar loads beside the bin maps' (make_arm_walk): the joint, and up to four groups of one or two
-// neighbouring spheres looked up together.  Groups past the fourth of a link
-// lie in extra[x_begin .. x_end).
+// wide scalar loads beside the bin maps' (make_arm_walk): the joint, and up to
+// four groups of one or two neighbouring spheres looked up together.  Groups past
+// the fourth of a link lie in extra[x_begin .. x_end).
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 struct ArmGroups {

@@ -4,9 +4,10 @@
 // straight line failed while both endpoints are collision-free.
 //
 // One wave per call, persistent over the candidate list.  A call is a chain
-// of dependent wave steps (sample, nearest node, extension check) that leaves
-// most of a wave's issue slots to latency, so what counts is how few
-// instructions a step takes and how many waves a CU holds.
+// of dependent wave steps (sample, nearest node, extension check): a wave alone
+// on its SIMD issues a vector instruction in a quarter of its cycles, sixteen
+// waves a CU in 0.86 of them, so what counts is how few instructions a step
+// takes and how many waves a CU holds.
 //   vectors  a configuration is spread over the lanes (lane holds component
 //            lane mod 8), so steering and the ellipsoid's map cost one
 //            instruction where a copy per lane costs eight;
@@ -28,11 +29,11 @@
 //            axis) pairs and then (state, sphere) pairs over the lanes, each
 //            sphere tested exactly against the obstacles its bins list;
 //            otherwise the states share the lanes, which split the obstacles.
-// Arm of 40 spheres, 30 obstacles, M 6, N 100, trees of 512: k_rrtc 1.83 ms at
+// Arm of 40 spheres, 30 obstacles, M 6, N 100, trees of 512: k_rrtc 1.81 ms at
 // budget 100 where whole states per lane, every sphere against every obstacle
-// and four waves per CU took 19.7 ms; a plan with the repair 2.7 against 26 ms
-// at budget 100, 9.7 against 66 at 400, 38 against 125 at 1000 (where most
-// calls run again).
+// and four waves per CU took 19.7 ms (scene seed 5); a plan with the repair 2.45
+// against 25 ms at budget 100, 9.7 against 63 at 400, 38 against 120 at 1000,
+// where most calls run again (scene seed 0).
 // This file is compiled without floating-point contraction: sampling, nearest
 // node and steering are FP32 computations with a fixed operation order (see
 // include/gtmp.h), so the trees are reproducible bit for bit.
@@ -62,7 +63,7 @@ struct RrtcArgs {
     float eta, res, ell_factor;
     uint32_t k0, k1, stage;
     const uint32_t *stage_dev;  // when set, the stage is read here at kernel start (replayed graphs)
-    unsigned long long *stats;  // calls, successes, iterations, nodes, states checked, nearest-node distances
+    unsigned long long *stats;  // calls, successes, iterations, nodes, states checked (whole rounds), distances
     // single-edge outputs (path mode)
     float *path;
     int32_t *path_count;
@@ -382,7 +383,9 @@ struct RrtcCall {
     }
 
     // Whether the segment p -> qn (a tree node and the new one) is free at
-    // its states 1 .. Hs - 1, counting the states as rounds of up to 64.
+    // its states 1 .. Hs - 1, counted in rounds of up to 64 (with the bins eight
+    // states are evaluated at a time, fewer than are counted where one is in
+    // contact).
     __device__ __forceinline__ bool segment_free(float vp, float vqn, int Hs) {
         const float den = (float)(Hs - 1);
         if constexpr (WORDS > 0) {
